@@ -30,6 +30,7 @@ struct clue_ctx {
   float r1 = -1.0f;  // nearest-higher first radius; negative: default d_m / 4
   int quads = 1;      // density strategy (1 quads by search, 2 per-query merge, 3 quads by merge)
   int expansion = 1;  // labels: 1 pointer jumping, 2 depth-first walk per seed
+  bool tuned = false; // clue_set_tuning was called: every run takes the tiled kernels it describes
   LaunchCfg cfg{};
   hipStream_t cap_stream = nullptr;
   hipGraph_t graph = nullptr;
@@ -499,7 +500,9 @@ static int run_common(clue_ctx* c, int64_t n, int32_t n_events, int32_t event_ba
     if (rc != CLUE_OK) return rc;
   }
   hipEvent_t* ev = c->timing ? c->ev : nullptr;
-  if (!batched) {
+  if (!c->tuned && n <= kDirectMax) {
+    HIP_TRY(c, launch_direct(c->g, c->a, d, s, ev));
+  } else if (!batched) {
     LaunchCfg cfg = c->cfg;
     cfg.graph_mode = false;
     HIP_TRY(c, launch_pipeline(c->g_plain, c->a, d, cfg, s, ev));
@@ -760,6 +763,7 @@ int clue_set_tuning(clue_ctx* c, const clue_tuning* t) {
       return rc;
     }
   }
+  c->tuned = true;
   c->tile = tile;
   c->tpq = tpq;
   c->bx = bx;
@@ -903,6 +907,11 @@ int clue_run_noalloc(const clue_params* p, const clue_tuning* t, int64_t n, cons
   d.event_base = 0;
   d.cluster_id = cluster_id;
   d.is_seed = is_seed;
+  if (!t && n <= kDirectMax) {
+    e = launch_direct(g, a, d, (hipStream_t)stream, nullptr);
+    if (e != hipSuccess) return set_err(nullptr, CLUE_ERR_HIP, std::string("kernel launch: ") + hipGetErrorString(e));
+    return CLUE_OK;
+  }
   // plain launches, sized to the run; the first kernel clears every counter,
   // tile count and scan status the run reads, so the previous call's
   // contents do not matter

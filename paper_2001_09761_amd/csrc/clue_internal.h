@@ -37,6 +37,7 @@ constexpr int kBatchU = 8;         // ... and of the batched k_scatter, k_place 
                                    // per workgroup, and 2048-slot LDS chunks that keep more of a tile
                                    // or a parent chain on chip (single launches keep kPlaceU, for more
                                    // workgroups per event)
+constexpr int kDirectMax = 8192;   // hits of the largest run that takes the all-pairs form
 constexpr int kScatterBlocksPerCU = 2;  // persistent k_scatter workgroups per CU
 
 // Counters in device memory, cleared at the start of every run. Each sits on
@@ -176,6 +177,7 @@ struct LaunchCfg {
 // `ev` receives a HIP event after each stage when non-null.
 hipError_t launch_pipeline(const Geom& g, const Arena& a, const RunDesc& d, const LaunchCfg& cfg,
                            hipStream_t s, hipEvent_t* ev);
+hipError_t launch_direct(const Geom& g, const Arena& a, const RunDesc& d, hipStream_t s, hipEvent_t* ev);
 hipError_t launch_set_desc(const RunDesc& d, RunDesc* dd, hipStream_t s);
 hipError_t launch_validate(const Geom& g, const Arena& a, const RunDesc& d, hipStream_t s);
 int occupancy_blocks_per_cu(int which, int lds_bytes);
