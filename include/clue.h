@@ -206,8 +206,8 @@ typedef struct {
   int32_t threads_per_query; /* lanes per full-window nearest-higher query: 1, 2, 4, 8 */
   int32_t block_x, block_y; /* tiles per work item (1..16 each) */
   int32_t lds_cap;          /* hits staged in LDS per work item (64..2048, default
-                               960); denser items are split into quarter blocks,
-                               then single tiles; a tile still too dense is
+                               960); denser items are halved, down to
+                               single tiles; a tile still too dense is
                                searched in global memory by a follow-up kernel
                                that spreads its queries over the whole GPU */
   float nh_first_radius;    /* radius (cm) of the first nearest-higher pass; a hit

@@ -546,10 +546,10 @@ __global__ __launch_bounds__(kWG) void k_scan(DescArg<G> dg, Geom g, Arena a) {
 // ---------------------------------------------------------------------------
 // Tile-block work items. An item is one (event, layer) unit and a block of
 // bx*by tiles (the core); its staged region adds `halo` tiles around the core
-// (clamped to the grid). Dense blocks whose region does not fit in LDS are
-// processed as four quarter blocks, a quarter that still does not fit one
-// core tile at a time, and a tile whose own region does not fit is queued
-// for the stage's spill kernel, which searches global memory.
+// (clamped to the grid). A block whose region does not fit in LDS is halved
+// along its longer side, and so on down to single tiles (BlockWalk); a tile
+// whose own region does not fit is queued for the stage's spill kernel, which
+// searches global memory.
 // ---------------------------------------------------------------------------
 struct Region {
   int unit;       // event * L + layer
@@ -665,6 +665,45 @@ __device__ __forceinline__ void core_query(const RegionLds& L, const Region& R, 
 }
 
 __device__ __forceinline__ int slot_of(const RegionLds& L, int row, int p) { return L.row_gs[row] + (p - L.row_lo[row]); }
+
+// The rectangles that a block's core is processed in. Halving stages less halo
+// than quartering did: a 10 x 10 block with a one-tile halo that overflows
+// stages 2 x 84 tiles instead of 4 x 49 (one event of uneven layers, whose
+// densest overflow a 10 x 10 block: density 67 -> 53 us, nearest-higher 76 ->
+// 57 us; the paper's workload, 1M hits of 3 cm clusters: 828 -> 614 us a run).
+// Rectangles are relative to the block (at most 16 tiles a side), four bits per
+// bound; those still to do wait on an LDS stack (each halving of at most 4 + 4
+// leaves one). Every lane keeps the same state; lane 0 writes the stack, and
+// region_setup's barriers lie between any write and read of one entry.
+struct BlockWalk {
+  int x0, y0, x1, y1;  // the current rectangle, inclusive
+  int depth;
+  unsigned short* stack;
+  static constexpr int kDepth = 8;
+  __device__ __forceinline__ BlockWalk(unsigned short* s, int w, int h)
+      : x0(0), y0(0), x1(w - 1), y1(h - 1), depth(0), stack(s) {}
+  __device__ __forceinline__ bool single() const { return x0 == x1 && y0 == y1; }
+  // Keeps the first half as the current rectangle.
+  __device__ __forceinline__ void split() {
+    const bool wide = x1 - x0 >= y1 - y0;
+    const int mx = (x0 + x1) >> 1, my = (y0 + y1) >> 1;
+    if (threadIdx.x == 0)
+      stack[depth] = (unsigned short)((wide ? mx + 1 : x0) | (wide ? y0 : my + 1) << 4 | x1 << 8 | y1 << 12);
+    ++depth;
+    x1 = wide ? mx : x1;
+    y1 = wide ? y1 : my;
+  }
+  // The next rectangle; false when none is left.
+  __device__ __forceinline__ bool next() {
+    if (depth == 0) return false;
+    const unsigned v = stack[--depth];
+    x0 = v & 15;
+    y0 = (v >> 4) & 15;
+    x1 = (v >> 8) & 15;
+    y1 = v >> 12;
+    return true;
+  }
+};
 
 // Work-item scheduling. Items are (event, layer, tile block) triples in
 // row-major block order, so consecutive items are spatially adjacent and
@@ -1348,6 +1387,7 @@ __global__ __launch_bounds__(kWG, density_min_waves(MAXL, K)) void k_density(Des
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int s_rows[kRowMetaInts];
   __shared__ int s_item;
+  __shared__ unsigned short s_stack[BlockWalk::kDepth];
   const Staged<MAXL> S{smem, g.lds_cap};
   unsigned short* stile = reinterpret_cast<unsigned short*>(smem + 16 * g.lds_cap);  // both layouts: 16 B per hit
   unsigned short* qidx = reinterpret_cast<unsigned short*>(smem + density_qidx_offset(g.lds_cap));
@@ -1364,37 +1404,23 @@ __global__ __launch_bounds__(kWG, density_min_waves(MAXL, K)) void k_density(Des
   for (int item; (item = next_item<G>(st, n_items, &a.counters[C_QUEUE_RHO], &s_item)) >= 0;) {
     int unit, tx0, ty0, tx1, ty1;
     item_block(g, item, unit, tx0, ty0, tx1, ty1);
-    Region R;
-    make_region(g, unit, tx0, ty0, tx1, ty1, R);
-    region_setup(g, a, R, L);
-    if (L.core_lo[R.ch] == 0) continue;
-    if (R.total <= g.lds_cap) {
-      density_staged<MAXL, K>(g, a, R, L, S, stile, qidx, sent, keep);
-      continue;
-    }
-    // too dense: the four quarter blocks, then single tiles
-    const int hx = (tx1 - tx0 + 2) >> 1, hy = (ty1 - ty0 + 2) >> 1;
-    for (int sy = ty0; sy <= ty1; sy += hy)
-      for (int sx = tx0; sx <= tx1; sx += hx) {
-        const int ex = min(sx + hx - 1, tx1), ey = min(sy + hy - 1, ty1);
-        make_region(g, unit, sx, sy, ex, ey, R);
-        region_setup(g, a, R, L);
-        if (L.core_lo[R.ch] == 0) continue;
+    BlockWalk B(s_stack, tx1 - tx0 + 1, ty1 - ty0 + 1);
+    for (bool more = true; more;) {
+      Region R;
+      make_region(g, unit, tx0 + B.x0, ty0 + B.y0, tx0 + B.x1, ty0 + B.y1, R);
+      region_setup(g, a, R, L);
+      if (L.core_lo[R.ch] > 0) {
         if (R.total <= g.lds_cap) {
           density_staged<MAXL, K>(g, a, R, L, S, stile, qidx, sent, keep);
+        } else if (B.single()) {
+          spill_region(g, a, R, C_SPILL_RHO, kWG);
+        } else {
+          B.split();
           continue;
         }
-        for (int ty = sy; ty <= ey; ++ty)
-          for (int tx = sx; tx <= ex; ++tx) {
-            make_region(g, unit, tx, ty, tx, ty, R);
-            region_setup(g, a, R, L);
-            if (L.core_lo[R.ch] == 0) continue;
-            if (R.total <= g.lds_cap)
-              density_staged<MAXL, K>(g, a, R, L, S, stile, qidx, sent, keep);
-            else
-              spill_region(g, a, R, C_SPILL_RHO, kWG);
-          }
       }
+      more = B.next();
+    }
   }
 }
 
@@ -1694,48 +1720,31 @@ __device__ __forceinline__ void nh_global_region(const Geom& g, const Arena& a, 
 template <bool STRICT>
 __device__ __forceinline__ void nh_item(const Geom& g, const Arena& a, const RunDesc& d, int item, RegionLds& L,
                                         float4* rec, unsigned short* queue, unsigned char* prow, unsigned short* coreq,
-                                        int* s_qn) {
+                                        int* s_qn, unsigned short* s_stack) {
   int unit, tx0, ty0, tx1, ty1;
   item_block(g, item, unit, tx0, ty0, tx1, ty1);
-  Region R;
-  make_region(g, unit, tx0, ty0, tx1, ty1, R);
-  region_setup(g, a, R, L);
-  if (L.core_lo[R.ch] == 0) return;
-  const int ev_first = event_first_hit(a, d, R.e);
-  if (event_first_hit(a, d, R.e + 1) - ev_first > kPackedEventMax) {
-    // an event too large for the packed index word: the spill kernel searches
-    // global memory, where records carry caller indices
-    spill_region(g, a, R, C_SPILL_NH, kWG / g.tpq);
-    return;
-  }
-  if (R.total <= g.lds_cap) {
-    if (!nh_staged<STRICT>(g, a, d, R, L, rec, queue, prow, coreq, s_qn, ev_first)) nh_global_region<STRICT>(g, a, d, R, L, ev_first);
-    return;
-  }
-  // too dense: the four quarter blocks, then single tiles
-  const int hx = (tx1 - tx0 + 2) >> 1, hy = (ty1 - ty0 + 2) >> 1;
-  for (int sy = ty0; sy <= ty1; sy += hy)
-    for (int sx = tx0; sx <= tx1; sx += hx) {
-      const int ex = min(sx + hx - 1, tx1), ey = min(sy + hy - 1, ty1);
-      make_region(g, unit, sx, sy, ex, ey, R);
-      region_setup(g, a, R, L);
-      if (L.core_lo[R.ch] == 0) continue;
-      if (R.total <= g.lds_cap && nh_staged<STRICT>(g, a, d, R, L, rec, queue, prow, coreq, s_qn, ev_first)) continue;
-      if (R.total <= g.lds_cap) {
-        nh_global_region<STRICT>(g, a, d, R, L, ev_first);
+  const int e = unit / g.L;
+  const int ev_first = event_first_hit(a, d, e);
+  // an event too large for the packed index word: the spill kernel searches
+  // global memory, where records carry caller indices
+  const bool large = event_first_hit(a, d, e + 1) - ev_first > kPackedEventMax;
+  BlockWalk B(s_stack, tx1 - tx0 + 1, ty1 - ty0 + 1);
+  for (bool more = true; more;) {
+    Region R;
+    make_region(g, unit, tx0 + B.x0, ty0 + B.y0, tx0 + B.x1, ty0 + B.y1, R);
+    region_setup(g, a, R, L);
+    if (L.core_lo[R.ch] > 0) {
+      if (large || (R.total > g.lds_cap && B.single())) {
+        spill_region(g, a, R, C_SPILL_NH, kWG / g.tpq);
+      } else if (R.total > g.lds_cap) {
+        B.split();
         continue;
+      } else if (!nh_staged<STRICT>(g, a, d, R, L, rec, queue, prow, coreq, s_qn, ev_first)) {
+        nh_global_region<STRICT>(g, a, d, R, L, ev_first);
       }
-      for (int ty = sy; ty <= ey; ++ty)
-        for (int tx = sx; tx <= ex; ++tx) {
-          make_region(g, unit, tx, ty, tx, ty, R);
-          region_setup(g, a, R, L);
-          if (L.core_lo[R.ch] == 0) continue;
-          if (R.total > g.lds_cap)
-            spill_region(g, a, R, C_SPILL_NH, kWG / g.tpq);
-          else if (!nh_staged<STRICT>(g, a, d, R, L, rec, queue, prow, coreq, s_qn, ev_first))
-            nh_global_region<STRICT>(g, a, d, R, L, ev_first);
-        }
     }
+    more = B.next();
+  }
 }
 
 // Nearest-higher of the spilled queries, tpq lanes per query, from global
@@ -1778,6 +1787,7 @@ __global__ __launch_bounds__(kWG, 8) void k_nearest_higher(DescArg<G> dg, Geom g
   __shared__ int s_rows[kRowMetaInts];
   __shared__ int s_qn;
   __shared__ int s_item;
+  __shared__ unsigned short s_stack[BlockWalk::kDepth];
   float4* rec = reinterpret_cast<float4*>(smem);
   unsigned short* queue = reinterpret_cast<unsigned short*>(rec + g.lds_cap);
   unsigned short* coreq = queue + g.lds_cap;
@@ -1786,7 +1796,7 @@ __global__ __launch_bounds__(kWG, 8) void k_nearest_higher(DescArg<G> dg, Geom g
   const int n_items = d.n_events * g.L * g.bpu;
   ItemSched st{0, G ? xcc_id() : 0};
   for (int item; (item = next_item<G>(st, n_items, &a.counters[C_QUEUE_NH], &s_item)) >= 0;)
-    nh_item<STRICT>(g, a, d, item, L, rec, queue, prow, coreq, &s_qn);
+    nh_item<STRICT>(g, a, d, item, L, rec, queue, prow, coreq, &s_qn, s_stack);
 }
 
 // ---------------------------------------------------------------------------
