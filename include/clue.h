@@ -79,7 +79,9 @@ typedef struct {
   float x_min, y_min, x_max, y_max; /* extent of the fixed grid; hits outside
                                        are binned into the edge tiles */
   int32_t n_layers;          /* layer ids in [0, n_layers) */
-  float tile_size;           /* grid tile side (cm); <= 0: default */
+  float tile_size;           /* grid tile side (cm); <= 0: default. Unless
+                                clue_set_tuning is called, runs may use a larger
+                                tile than this one (results do not depend on it) */
   int32_t threads_per_query; /* lanes per nearest-higher query (1, 2, 4); <= 0: default */
   uint32_t flags;            /* CLUE_* flags above */
   int32_t kernel;            /* chi of Eq. 3 (Sec. 2.2): CLUE_KERNEL_FLAT (chi = 1),

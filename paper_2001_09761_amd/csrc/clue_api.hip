@@ -26,11 +26,12 @@ struct clue_ctx {
   float tile = 0.0f;
   int tpq = 1, bx = 8, by = 8, lds_cap = kDefaultLdsCap;
   int plain_cap = 0;  // LDS cap of the plain form (clue_run); 0: lds_cap
-  Geom g_plain{};     // g with the plain form's LDS cap
+  Geom g_plain{};     // geometry of the plain form's current run
+  Geom g_batch{};     // ... and of the batched form's runs
   float r1 = -1.0f;  // nearest-higher first radius; negative: default d_m / 4
   int quads = 1;      // density strategy (1 quads by search, 2 per-query merge, 3 quads by merge)
   int expansion = 1;  // labels: 1 pointer jumping, 2 depth-first walk per seed
-  bool tuned = false; // clue_set_tuning was called: every run takes the tiled kernels it describes
+  bool tuned = false; // clue_set_tuning was called: every run takes the tiled kernels it describes, as it describes them
   LaunchCfg cfg{};
   hipStream_t cap_stream = nullptr;
   hipGraph_t graph = nullptr;
@@ -190,6 +191,41 @@ static int plan_geom(const clue_params& p, float tile, int tpq, int bx, int by, 
   return CLUE_OK;
 }
 
+// Geometry that a run of n hits in `units` layers uses when no tuning is set
+// (results do not depend on it). `req` is the requested one.
+//
+// Tile: where a density window could span three tiles, the next larger tile
+// whose windows span two, because only those take the merged quad lists (1M hits
+// of the paper's workload at its 5 cm bin: density 288 us with 5 cm tiles, 88 us
+// with 6.05 cm ones).
+//
+// Block: as many tiles a side as make its region (block and halo) hold 620 hits
+// on average, at most 10. At the default cap of 960 hits, that leaves room for
+// the layers' and clusters' fluctuations, for a region over the cap is staged in
+// halves. A run of 1M hits on 100 layers (4 hits per tile) took 189, 172 and
+// 203 us with blocks of 8, 10 and 12, the paper's (8.6 per tile) 263, 284, 294
+// and 306 us with 5, 6, 7 and 8, and 100,000 hits (0.4 per tile) 113, 93 and 93
+// us with 8, 10 and 16. Smaller blocks, down to 8, where there would be less than
+// four items per CU.
+static Geom run_geom(const clue_params& p, const Geom& req, int tpq, int lds_cap, float r1, int quads,
+                     int expansion, double n, double units) {
+  constexpr double kRegionHits = 620.0;
+  std::string msg;
+  float tile = p.tile_size;
+  Geom g = req;
+  if (req.maxl > 2) {
+    tile = (float)(2.0 * (double)p.dc * (1.0 + 1.0 / 128.0));
+    if (plan_geom(p, tile, tpq, 1, 1, lds_cap, r1, quads, expansion, g, msg) != CLUE_OK) return req;
+  }
+  const double per_tile = n / (units * g.tpl);
+  int b = 10;
+  if (per_tile * (10.0 + 2 * g.halo) * (10.0 + 2 * g.halo) > kRegionHits)
+    b = std::max(1, (int)std::sqrt(kRegionHits / per_tile) - 2 * g.halo);
+  while (b > 8 && units * ((g.nx + b - 1) / b) * ((g.ny + b - 1) / b) < 1024.0) --b;
+  if (plan_geom(p, tile, tpq, b, b, lds_cap, r1, quads, expansion, g, msg) != CLUE_OK) return req;
+  return g;
+}
+
 // ---------------------------------------------------------------------------
 // Arena layout.
 // ---------------------------------------------------------------------------
@@ -286,17 +322,27 @@ static void drop_graph(clue_ctx* c) {
   c->graph = nullptr;
 }
 
-static void compute_cfg(clue_ctx* c) {
-  const int lds = lds_bytes_for(c->g);
+// Geometry of a run of n hits in n_events events: the context's own once a
+// tuning has been set.
+static Geom ctx_geom(const clue_ctx* c, int64_t n, int32_t n_events) {
+  if (c->tuned) return c->g;
+  return run_geom(c->params, c->g, c->tpq, c->lds_cap, c->r1, c->quads, c->expansion, (double)n,
+                  (double)n_events * c->g.L);
+}
+
+// The batched form's geometry and the persistent grids, for the capacity (N, E).
+static void compute_cfg(clue_ctx* c, int64_t N, int32_t E) {
+  c->g_batch = ctx_geom(c, N, E);
+  const int lds = lds_bytes_for(c->g_batch);
   // a multiple of kQueues: streaming kernels give each XCD one run of chunks
   c->cfg.persist_blocks_stream = (c->n_cu * std::min(occupancy_blocks_per_cu(0, 0), 8) + kQueues - 1) / kQueues * kQueues;
   c->cfg.persist_blocks_scatter = (c->n_cu * kScatterBlocksPerCU + kQueues - 1) / kQueues * kQueues;
   c->cfg.persist_blocks_rho = c->n_cu * occupancy_blocks_per_cu(1, lds);
-  c->cfg.persist_blocks_nh = c->n_cu * occupancy_blocks_per_cu(3, lds_bytes_nh(c->g));
+  c->cfg.persist_blocks_nh = c->n_cu * occupancy_blocks_per_cu(3, lds_bytes_nh(c->g_batch));
   if (std::getenv("CLUE_VERBOSE"))
     std::fprintf(stderr, "clue: persistent grids stream=%d rho=%d nh=%d scan=%d (cu=%d, lds rho=%d nh=%d)\n",
                  c->cfg.persist_blocks_stream, c->cfg.persist_blocks_rho, c->cfg.persist_blocks_nh,
-                 c->cfg.persist_blocks_scan, c->n_cu, lds, lds_bytes_nh(c->g));
+                 c->cfg.persist_blocks_scan, c->n_cu, lds, lds_bytes_nh(c->g_batch));
   c->cfg.persist_blocks_scan = c->n_cu * std::min(occupancy_blocks_per_cu(2, 0), 4);
 }
 
@@ -341,7 +387,7 @@ static int ensure_graph(clue_ctx* c) {
   LaunchCfg cfg = c->cfg;
   cfg.graph_mode = true;
   HIP_TRY(c, hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
-  hipError_t le = launch_pipeline(c->g, c->a, d, cfg, c->cap_stream, nullptr);
+  hipError_t le = launch_pipeline(c->g_batch, c->a, d, cfg, c->cap_stream, nullptr);
   hipGraph_t graph = nullptr;
   hipError_t ce = hipStreamEndCapture(c->cap_stream, &graph);
   if (le != hipSuccess) {
@@ -419,7 +465,7 @@ int clue_create(clue_ctx** out, const clue_params* p, int hip_device, int64_t ma
       return CLUE_ERR_HIP;
     }
   }
-  compute_cfg(c);
+  compute_cfg(c, max_hits, max_events);
   rc = alloc_arena(c, max_hits, max_events);
   if (rc != CLUE_OK) {
     g_create_err = c->err;
@@ -435,7 +481,11 @@ int clue_reserve(clue_ctx* c, int64_t max_hits, int32_t max_events) {
   if (max_hits < 0 || max_hits >= ((int64_t)1 << 31) - 1 || max_events < 1)
     return set_err(c, CLUE_ERR_ARG, "capacity out of range");
   if (max_hits <= c->a.cap_hits && max_events <= c->a.cap_events) return CLUE_OK;
-  return alloc_arena(c, std::max<int64_t>(max_hits, c->a.cap_hits), std::max(max_events, c->a.cap_events));
+  max_hits = std::max<int64_t>(max_hits, c->a.cap_hits);
+  max_events = std::max(max_events, c->a.cap_events);
+  const int rc = alloc_arena(c, max_hits, max_events);
+  if (rc == CLUE_OK) compute_cfg(c, max_hits, max_events);
+  return rc;
 }
 
 static int check_run_args(clue_ctx* c, int64_t n, int32_t n_events, const void* x, const void* y, const void* layer,
@@ -482,9 +532,11 @@ static int run_common(clue_ctx* c, int64_t n, int32_t n_events, int32_t event_ba
   HIP_TRY(c, hipSetDevice(c->device));
   hipStream_t s = (hipStream_t)stream;
   RunDesc d{};
-  // the plain form may stage a different number of hits per work item
-  c->g_plain = c->g;
-  if (c->plain_cap > 0) c->g_plain.lds_cap = c->plain_cap;
+  if (!batched) {
+    c->g_plain = ctx_geom(c, n, 1);
+    // the plain form may stage a different number of hits per work item
+    if (c->plain_cap > 0) c->g_plain.lds_cap = c->plain_cap;
+  }
   d.n = (int32_t)n;
   d.n_events = n_events;
   d.x = x;
@@ -511,7 +563,7 @@ static int run_common(clue_ctx* c, int64_t n, int32_t n_events, int32_t event_ba
     if (ev) {
       LaunchCfg cfg = c->cfg;
       cfg.graph_mode = true;
-      HIP_TRY(c, launch_pipeline(c->g, c->a, d, cfg, s, ev));
+      HIP_TRY(c, launch_pipeline(c->g_batch, c->a, d, cfg, s, ev));
     } else {
       rc = ensure_graph(c);
       if (rc != CLUE_OK) return rc;
@@ -752,18 +804,20 @@ int clue_set_tuning(clue_ctx* c, const clue_tuning* t) {
   const bool regrow =
       (int64_t)c->a.cap_events * g.L * g.tpl + 1 > c->a.cap_tiles || (builds_lists(g) && !c->a.flist);
   const Geom old = c->g;
+  const bool old_tuned = c->tuned;
   c->g = g;
+  c->tuned = true;
   drop_graph(c);
-  compute_cfg(c);
+  compute_cfg(c, c->a.cap_hits, c->a.cap_events);
   if (regrow) {
     rc = alloc_arena(c, c->a.cap_hits, c->a.cap_events);
     if (rc != CLUE_OK) {
       c->g = old;
-      compute_cfg(c);
+      c->tuned = old_tuned;
+      compute_cfg(c, c->a.cap_hits, c->a.cap_events);
       return rc;
     }
   }
-  c->tuned = true;
   c->tile = tile;
   c->tpq = tpq;
   c->bx = bx;
@@ -896,6 +950,7 @@ int clue_run_noalloc(const clue_params* p, const clue_tuning* t, int64_t n, cons
   rc = scratch_on_device(dev, &base);
   if (rc != CLUE_OK) return rc;
   const Arena a = arena_at((char*)base, g, P, n, 1);
+  if (!t) g = run_geom(*p, g, tpq, cap, r1, quads, expansion, (double)n, (double)g.L);
   RunDesc d{};
   d.n = (int32_t)n;
   d.n_events = 1;
