@@ -12,7 +12,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libclue.so")
-SOURCES = [os.path.join(CSRC, f) for f in ("clue_kernels.hip", "clue_direct.hip", "clue_api.hip")]
+SOURCES = [os.path.join(CSRC, f) for f in ("clue_kernels.hip", "clue_direct.hip", "clue_units.hip", "clue_api.hip")]
 
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [

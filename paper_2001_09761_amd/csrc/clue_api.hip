@@ -188,7 +188,19 @@ static int plan_geom(const clue_params& p, float tile, int tpq, int bx, int by, 
   g.lds_cap = lds_cap;
   g.ts_ints = rh * (rw + 1) + 1;
   g.q_ints = (bx + 1) * (by + 1) + 1;
+  g.units = 0;
   return CLUE_OK;
+}
+
+// Workgroups of k_units for a run of n hits (each takes 1024 hits at a time) in
+// one event, or for the batched form with n = 0 any run up to its capacity; 0
+// when the unit path is not to be tried: the depth-first expansion walks the
+// general path's lists, a layer's tile counts have to fit in LDS, and so do
+// most units.
+static int units_grid(const Geom& g, int64_t n, int64_t capacity) {
+  if (g.expand || g.tpl > kUnitTiles || n > (int64_t)g.L * kUnitAvg) return 0;
+  if (n == 0) n = capacity;
+  return (int)(std::max<int64_t>(1, std::min<int64_t>((n + 1023) / 1024, 1024) + kQueues - 1) / kQueues * kQueues);
 }
 
 // Geometry that a run of n hits in `units` layers uses when no tuning is set
@@ -557,9 +569,11 @@ static int run_common(clue_ctx* c, int64_t n, int32_t n_events, int32_t event_ba
   } else if (!batched) {
     LaunchCfg cfg = c->cfg;
     cfg.graph_mode = false;
+    c->g_plain.units = units_grid(c->g_plain, n, n);
     HIP_TRY(c, launch_pipeline(c->g_plain, c->a, d, cfg, s, ev));
   } else {
     HIP_TRY(c, launch_set_desc(d, c->a.desc, s));
+    c->g_batch.units = units_grid(c->g_batch, 0, c->a.cap_hits);
     if (ev) {
       LaunchCfg cfg = c->cfg;
       cfg.graph_mode = true;
@@ -972,6 +986,7 @@ int clue_run_noalloc(const clue_params* p, const clue_tuning* t, int64_t n, cons
   // contents do not matter
   LaunchCfg cfg{};
   cfg.graph_mode = false;
+  g.units = units_grid(g, n, n);
   if (g.expand) {  // the k-way walk's grid: one run of workgroups per XCD
     int ncu = 0;
     e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);

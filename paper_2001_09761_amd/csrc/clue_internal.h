@@ -38,6 +38,9 @@ constexpr int kBatchU = 8;         // ... and of the batched k_scatter, k_place 
                                    // or a parent chain on chip (single launches keep kPlaceU, for more
                                    // workgroups per event)
 constexpr int kDirectMax = 8192;   // hits of the largest run that takes the all-pairs form
+constexpr int kUnitMax = 11264;      // hits of the largest unit the unit path takes
+constexpr int kUnitAvg = 10240;      // ... and of the largest mean unit it is tried for
+constexpr int kUnitTiles = 2816;     // tiles of the largest layer grid it takes
 constexpr int kScatterBlocksPerCU = 2;  // persistent k_scatter workgroups per CU
 
 // Counters in device memory, cleared at the start of every run. Each sits on
@@ -48,6 +51,7 @@ constexpr int kQueues = 8;          // one per XCD
 enum Counter {
   C_TICKET_TILES = 0,                           // chunk tickets of the tile-count scan
   C_TICKET_SEEDS = 1 * kCounterStride,          // chunk tickets of the seed / follower scan
+  C_UNITS = C_TICKET_TILES + kCounterStride / 2,  // 1: this run takes the unit path
   C_QUEUE_RHO = 2 * kCounterStride,             // kQueues heads for the density stage
   C_QUEUE_NH = (2 + kQueues) * kCounterStride,  // kQueues heads for the nearest-higher stage
   C_SPILL_RHO = (2 + 2 * kQueues) * kCounterStride,      // density query chunks left to the spill kernel
@@ -105,6 +109,7 @@ struct Geom {
   int32_t nh_phase1;  // nearest-higher first searches radius r1 < dm
   float r1sq;       // fl(r1*r1)
   float win_r1;     // r1 (1 + 2^-10)
+  int32_t units;    // 0, or the workgroups of k_units: the unit path is tried first
   int32_t expand;   // cluster expansion: 0 pointer jumping, 1 depth-first from each seed
   uint32_t flags;   // CLUE_* flags
 };
@@ -122,6 +127,7 @@ struct Arena {
                          //       of each query chunk)
                          //       (the depth-first expansion reuses both for each
                          //       follower's owner and its position in the owner's list)
+                         //       (the unit path keeps its arrays at their ends)
                          //       (the grid build keeps arrival-order hit ids and tiles
                          //       in the rho and parent buffers until each tile is
                          //       ordered by hit index)

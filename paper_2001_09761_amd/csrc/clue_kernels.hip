@@ -2,6 +2,8 @@
 //
 // Stage map (arXiv:2001.09761):
 //   k_clear            clears counters, tile counts and scan status
+//   (k_units, k_unit_sort and k_unit_finish, in clue_units.hip, take the place of
+//   the other grid-build and label kernels when the hits come grouped by layer)
 //   k_hist             fixed grid, part 1: atomic per-tile histogram (Sec. 2.1)
 //   k_scan<TILES>      exclusive prefix scan of the tile counts (decoupled look-back)
 //   k_scatter          fixed grid, part 2: hit ids into the tile CSR (arrival order)
@@ -39,33 +41,8 @@ const char* const kStageNames[S_COUNT] = {"clear",        "grid_hist",  "grid_sc
                                           "follower_lists"};
 
 // ---------------------------------------------------------------------------
-// Run descriptor: by value (plain launches) or from device memory (graph).
-// ---------------------------------------------------------------------------
-template <bool G>
-struct DescArg;
-template <>
-struct DescArg<false> {
-  RunDesc d;
-  __device__ __forceinline__ RunDesc get() const { return d; }
-};
-template <>
-struct DescArg<true> {
-  const RunDesc* p;
-  __device__ __forceinline__ RunDesc get() const { return *p; }
-};
-
-// ---------------------------------------------------------------------------
 // Geometry helpers.
 // ---------------------------------------------------------------------------
-
-// Tile coordinate of a position: floor((v - origin) / T) clamped to the grid.
-// Monotone non-decreasing in v, which is what makes the query windows below
-// supersets of the true neighbourhoods.
-__device__ __forceinline__ int tile_coord(float v, float origin, float inv_t, int n) {
-  float t = floorf(__fmul_rn(__fsub_rn(v, origin), inv_t));
-  t = fminf(fmaxf(t, 0.0f), (float)(n - 1));
-  return (int)t;
-}
 
 // Half width of a query window: the radius inflated by 2^-10 relative plus
 // 2^-20 |v|, so that rounding of v +- w can never exclude a hit whose float32
@@ -74,167 +51,22 @@ __device__ __forceinline__ float window_half(float w, float v) {
   return __fadd_rn(w, __fmul_rn(fabsf(v), 0x1p-20f));
 }
 
-__device__ __forceinline__ int ld_relaxed(const int32_t* p) {
-  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-__device__ __forceinline__ void st_relaxed(int32_t* p, int v) {
-  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// First caller-order hit of event e, clamped to [0, n] (memory safety for
-// unvalidated event ids).
-__device__ __forceinline__ int event_first_hit(const Arena& a, const RunDesc& d, int e) {
-  return clampi(a.ev_start[e], 0, d.n);
-}
-
-// Seeds are marked by one bit per hit in caller order; the seed scan gives
-// the count before each 32-bit word. Words cover hits 0..n, so the rank of
-// n (the seed total) is defined too.
-__host__ __device__ __forceinline__ int64_t seed_words(int64_t n) { return n / 32 + 1; }
-// Seeds among caller hits 0..h-1 (h in [0, n]).
-__device__ __forceinline__ int seed_rank(const Arena& a, int h) {
-  return a.seed_wrank[h >> 5] + __popc(a.seedbits[h >> 5] & ((1u << (h & 31)) - 1u));
-}
-
-// Event of tile-CSR slot s: slots are ordered by (event, layer, tile), so the
-// event is the last e whose first tile starts at or before s.
-__device__ __forceinline__ int event_of_slot(const Geom& g, const Arena& a, const RunDesc& d, int s) {
-  const int64_t per = (int64_t)g.L * g.tpl;
-  int lo = 0, hi = d.n_events - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (a.tile_start[mid * per] <= s)
-      lo = mid;
-    else
-      hi = mid - 1;
-  }
-  return lo;
-}
-
-// ---------------------------------------------------------------------------
-// Streaming kernels cut their index range into chunks of `chunk` consecutive
-// indices and give each XCD one contiguous run of chunks (workgroups are
-// dispatched to the XCDs round-robin by id; the grid is a multiple of
-// kQueues). Neighbouring indices share lines in the gathers and scattered
-// writes that follow, so they are fetched into, and completed in, one L2.
-// ---------------------------------------------------------------------------
-struct ChunkRun {
-  int c, end, step;
-};
-__device__ __forceinline__ ChunkRun xcd_run(int n, int chunk) {
-  const int nch = (int)(((int64_t)n + chunk - 1) / chunk);
-  const int x = (int)blockIdx.x % kQueues, i = (int)blockIdx.x / kQueues;
-  return {(int)((int64_t)nch * x / kQueues) + i, (int)((int64_t)nch * (x + 1) / kQueues),
-          (int)gridDim.x / kQueues};
-}
-
 // ---------------------------------------------------------------------------
 // k_clear
 // ---------------------------------------------------------------------------
 template <bool G>
 __global__ __launch_bounds__(kWG) void k_clear(DescArg<G> dg, Geom g, Arena a) {
-  const RunDesc d = dg.get();
-  const int64_t tt = (int64_t)d.n_events * g.L * g.tpl + 1;
-  const int64_t n1 = (int64_t)d.n + 1;
-  const bool fol = builds_lists(g);
-  const int64_t stride = (int64_t)gridDim.x * kWG;
-  const int64_t i0 = (int64_t)blockIdx.x * kWG + threadIdx.x;
-  for (int64_t i = i0; i < tt; i += stride) a.tile_start[i] = 0;
-  if (fol)
-    for (int64_t i = i0; i < n1; i += stride) a.fstart[i] = 0;
-  constexpr int64_t SC = (int64_t)kWG * scan_items(G);
-  const int64_t nchunk_t = (tt + SC - 1) / SC;
-  const int64_t nchunk_s = (n1 + SC - 1) / SC;
-  for (int64_t i = i0; i < nchunk_t && i < a.cap_chunks; i += stride) a.scan_status[i] = 0ull;
-  for (int64_t i = i0; i < nchunk_s && i < a.cap_chunks; i += stride) a.scan_status[a.cap_chunks + i] = 0ull;
+  const int64_t i0 = (int64_t)blockIdx.x * kWG + threadIdx.x, stride = (int64_t)gridDim.x * kWG;
   for (int64_t i = i0; i < C_COUNT; i += stride) a.counters[i] = 0;
-  for (int64_t i = i0; i <= d.n_events; i += stride) a.ev_start[i] = 0;
-  for (int64_t i = i0; i < seed_words(d.n); i += stride) a.seedbits[i] = 0u;
+  const RunDesc d = dg.get();
+  clear_grid(d, g, a, i0, stride);
+  clear_lists(d, g, a, i0, stride);
 }
 
-// ---------------------------------------------------------------------------
-// k_hist: tile of every hit, atomic count per tile, arrival rank kept.
-// Lanes of a wave that share a tile are grouped first, so each distinct tile
-// costs one atomic per wave (hits of a cluster tend to be adjacent in input
-// order); ranks within a group follow lane order. Each lane takes kPlaceU
-// hits per step so that their atomics are in flight together.
-// ---------------------------------------------------------------------------
 template <bool G>
 __global__ __launch_bounds__(kWG) void k_hist(DescArg<G> dg, Geom g, Arena a) {
   const RunDesc d = dg.get();
-  constexpr int U = kPlaceU;  // sub-batches per step; their atomics overlap
-  const int lane = threadIdx.x & 63;
-  for (ChunkRun r = xcd_run(d.n, kWG * U); r.c < r.end; r.c += r.step) {
-    const int h0 = r.c * kWG * U;  // uniform per workgroup
-    // every load of a lane is issued before its first store (the event
-    // starts below could alias the inputs as far as the compiler knows)
-    int t[U], ev[U], evp[U];
-#pragma unroll
-    for (int j = 0; j < U; ++j) {
-      const int h = h0 + j * kWG + (int)threadIdx.x;
-      t[j] = -1;
-      ev[j] = evp[j] = 0;
-      if (h < d.n) {
-        if (d.event) {
-          ev[j] = clampi(d.event[h] - d.event_base, 0, d.n_events - 1);
-          evp[j] = h == 0 ? -1 : clampi(d.event[h - 1] - d.event_base, 0, d.n_events - 1);
-        }
-        const int l = clampi(d.layer[h], 0, g.L - 1);
-        const int tx = tile_coord(d.x[h], g.x0, g.inv_t, g.nx);
-        const int ty = tile_coord(d.y[h], g.y0, g.inv_t, g.ny);
-        t[j] = l * g.tpl + ty * g.nx + tx;  // the event's part is added below
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < U; ++j) {
-      const int h = h0 + j * kWG + (int)threadIdx.x;
-      if (h >= d.n) continue;
-      const int e = ev[j];
-      t[j] += e * g.L * g.tpl;
-      if (d.event) {
-        for (int k = evp[j] + 1; k <= e; ++k) a.ev_start[k] = h;
-        if (h == d.n - 1)
-          for (int k = e + 1; k <= d.n_events; ++k) a.ev_start[k] = d.n;
-      } else if (h == 0) {
-        a.ev_start[0] = 0;
-        a.ev_start[1] = d.n;
-      }
-    }
-    int base[U], off[U], leader[U];
-#pragma unroll
-    for (int j = 0; j < U; ++j) {
-      const bool valid = t[j] >= 0;
-      unsigned long long todo = __ballot(valid);
-      int ld = lane, o = 0, cnt = 0;
-      while (todo) {  // wave-uniform: one pass per distinct tile in the wave
-        // the lowest unmatched lane leads; its tile is read into a scalar
-        // register, and a lane's offset is the count of its peers below it
-        const int l = __ffsll((long long)todo) - 1;
-        const int lt = __builtin_amdgcn_readlane(t[j], l);
-        const bool mine = t[j] == lt;  // invalid lanes (-1) never match a tile
-        const unsigned long long peers = __ballot(mine);
-        if (mine) {
-          ld = l;
-          o = __builtin_amdgcn_mbcnt_hi((unsigned)(peers >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)peers, 0u));
-          cnt = __popcll(peers);
-        }
-        todo &= ~peers;
-      }
-      base[j] = 0;
-      if (valid && lane == ld) base[j] = atomicAdd(&a.tile_start[t[j]], cnt);
-      off[j] = o;
-      leader[j] = ld;
-    }
-#pragma unroll
-    for (int j = 0; j < U; ++j) {
-      const int bs = __shfl(base[j], leader[j], 64);
-      const int h = h0 + j * kWG + (int)threadIdx.x;
-      if (t[j] >= 0) {
-        a.key[h] = t[j];
-        a.rank[h] = bs + off[j];
-      }
-    }
-  }
+  for (ChunkRun r = xcd_run(d.n, kHistChunk); r.c < r.end; r.c += r.step) hist_chunk<kPlaceU>(d, g, a, r.c * kHistChunk, d.n, (int)threadIdx.x);
 }
 
 // ---------------------------------------------------------------------------
@@ -247,95 +79,103 @@ __global__ __launch_bounds__(kWG) void k_hist(DescArg<G> dg, Geom g, Arena a) {
 // tile, so the counting loads are broadcasts from lines just read.
 // ---------------------------------------------------------------------------
 template <bool G>
-__global__ __launch_bounds__(kWG) void k_scatter(DescArg<G> dg, Geom g, Arena a) {
-  const RunDesc d = dg.get();
+__device__ __forceinline__ void scatter_chunk(const RunDesc& d, const Geom& g, const Arena& a, int chunk) {
   int* ids = reinterpret_cast<int*>(a.rho);
   constexpr int U = G ? kBatchU : kPlaceU;
-  for (ChunkRun rn = xcd_run(d.n, kWG * U); rn.c < rn.end; rn.c += rn.step) {
-    const int h0 = rn.c * kWG * U + (int)threadIdx.x;
-    int t[U], r[U];
+  const int h0 = chunk * kWG * U + (int)threadIdx.x;
+  int t[U], r[U];
 #pragma unroll
-    for (int j = 0; j < U; ++j) {
-      const int h = h0 + j * kWG;
-      t[j] = -1;
-      if (h < d.n) {
-        t[j] = a.key[h];
-        r[j] = a.rank[h];
-      }
+  for (int j = 0; j < U; ++j) {
+    const int h = h0 + j * kWG;
+    t[j] = -1;
+    if (h < d.n) {
+      t[j] = a.key[h];
+      r[j] = a.rank[h];
     }
+  }
 #pragma unroll
-    for (int j = 0; j < U; ++j) {
-      if (t[j] >= 0) {
-        const int s = a.tile_start[t[j]] + r[j];
-        ids[s] = h0 + j * kWG;
-        a.parent[s] = t[j];
-      }
+  for (int j = 0; j < U; ++j) {
+    if (t[j] >= 0) {
+      const int s = a.tile_start[t[j]] + r[j];
+      ids[s] = h0 + j * kWG;
+      a.parent[s] = t[j];
     }
   }
 }
 
 template <bool G>
-__global__ __launch_bounds__(kWG) void k_place(DescArg<G> dg, Geom g, Arena a) {
+__global__ __launch_bounds__(kWG) void k_scatter(DescArg<G> dg, Geom g, Arena a) {
+  if (by_units(g, a)) return;  // done unit by unit
   const RunDesc d = dg.get();
+  for (ChunkRun r = xcd_run(d.n, stream_chunk(G)); r.c < r.end; r.c += r.step) scatter_chunk<G>(d, g, a, r.c);
+}
+
+template <bool G>
+__device__ __forceinline__ void place_chunk(const RunDesc& d, const Geom& g, const Arena& a, int chunk) {
   const int* ids = reinterpret_cast<const int*>(a.rho);
   constexpr int U = G ? kBatchU : kPlaceU;
   constexpr int C = kWG * U;  // slots per chunk
   // the chunk's arrival-order ids in LDS: a hit's tile mostly lies inside
   // the chunk, so most of its counting reads are LDS reads
   __shared__ int s_ids[C];
-  for (ChunkRun rn = xcd_run(d.n, C); rn.c < rn.end; rn.c += rn.step) {
-    const int c0 = rn.c * C;
-    const int c1 = min(c0 + C, d.n);
+  const int c0 = chunk * C;
+  const int c1 = min(c0 + C, d.n);
 #pragma unroll
-    for (int j = 0; j < U; ++j) {
-      const int sl = c0 + (int)threadIdx.x + j * kWG;
-      s_ids[sl - c0] = sl < d.n ? ids[sl] : 0;
-    }
-    __syncthreads();
-    // slots in groups of four: a group's loads are all issued before its
-    // first store (which could alias them as far as the compiler knows)
-    constexpr int V = 4;
-#pragma unroll
-    for (int j0 = 0; j0 < U; j0 += V) {
-      int hv[V], s0v[V], s1v[V];
-      float xv[V], yv[V], ev[V];
-#pragma unroll
-      for (int k = 0; k < V; ++k) {
-        const int sl = c0 + (int)threadIdx.x + (j0 + k) * kWG;
-        hv[k] = -1;
-        if (sl < d.n) {
-          const int h = s_ids[sl - c0];
-          const int t = a.parent[sl];
-          hv[k] = h;
-          xv[k] = d.x[h];
-          yv[k] = d.y[h];
-          ev[k] = d.e[h];
-          s0v[k] = a.tile_start[t];
-          s1v[k] = a.tile_start[t + 1];
-        }
-      }
-#pragma unroll
-      for (int k = 0; k < V; ++k) {
-        if (hv[k] < 0) continue;
-        const int h = hv[k], s0 = s0v[k], s1 = s1v[k];
-        // the tile [s0, s1) in three parts: before the chunk, in it, after it
-        const int m0 = min(max(s0, c0), s1), m1 = max(min(s1, c1), m0);
-        int rk = 0;
-        for (int c = s0; c < m0; ++c) rk += ids[c] < h;
-        int c = m0;
-        for (; c + 3 < m1; c += 4)
-          rk += (s_ids[c - c0] < h) + (s_ids[c + 1 - c0] < h) + (s_ids[c + 2 - c0] < h) + (s_ids[c + 3 - c0] < h);
-        for (; c < m1; ++c) rk += s_ids[c - c0] < h;
-        for (c = m1; c < s1; ++c) rk += ids[c] < h;
-        const int slot = s0 + rk;
-        a.xs[slot] = xv[k];
-        a.ys[slot] = yv[k];
-        a.es[slot] = ev[k];
-        a.hs[slot] = h;
-      }
-    }
-    __syncthreads();  // the next chunk overwrites the staged ids
+  for (int j = 0; j < U; ++j) {
+    const int sl = c0 + (int)threadIdx.x + j * kWG;
+    s_ids[sl - c0] = sl < d.n ? ids[sl] : 0;
   }
+  __syncthreads();
+  // slots in groups of four: a group's loads are all issued before its
+  // first store (which could alias them as far as the compiler knows)
+  constexpr int V = 4;
+#pragma unroll
+  for (int j0 = 0; j0 < U; j0 += V) {
+    int hv[V], s0v[V], s1v[V];
+    float xv[V], yv[V], ev[V];
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+      const int sl = c0 + (int)threadIdx.x + (j0 + k) * kWG;
+      hv[k] = -1;
+      if (sl < d.n) {
+        const int h = s_ids[sl - c0];
+        const int t = a.parent[sl];
+        hv[k] = h;
+        xv[k] = d.x[h];
+        yv[k] = d.y[h];
+        ev[k] = d.e[h];
+        s0v[k] = a.tile_start[t];
+        s1v[k] = a.tile_start[t + 1];
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < V; ++k) {
+      if (hv[k] < 0) continue;
+      const int h = hv[k], s0 = s0v[k], s1 = s1v[k];
+      // the tile [s0, s1) in three parts: before the chunk, in it, after it
+      const int m0 = min(max(s0, c0), s1), m1 = max(min(s1, c1), m0);
+      int rk = 0;
+      for (int c = s0; c < m0; ++c) rk += ids[c] < h;
+      int c = m0;
+      for (; c + 3 < m1; c += 4)
+        rk += (s_ids[c - c0] < h) + (s_ids[c + 1 - c0] < h) + (s_ids[c + 2 - c0] < h) + (s_ids[c + 3 - c0] < h);
+      for (; c < m1; ++c) rk += s_ids[c - c0] < h;
+      for (c = m1; c < s1; ++c) rk += ids[c] < h;
+      const int slot = s0 + rk;
+      a.xs[slot] = xv[k];
+      a.ys[slot] = yv[k];
+      a.es[slot] = ev[k];
+      a.hs[slot] = h;
+    }
+  }
+  __syncthreads();  // the next chunk overwrites the staged ids
+}
+
+template <bool G>
+__global__ __launch_bounds__(kWG) void k_place(DescArg<G> dg, Geom g, Arena a) {
+  if (by_units(g, a)) return;  // done unit by unit
+  const RunDesc d = dg.get();
+  for (ChunkRun r = xcd_run(d.n, stream_chunk(G)); r.c < r.end; r.c += r.step) place_chunk<G>(d, g, a, r.c);
 }
 
 // ---------------------------------------------------------------------------
@@ -357,189 +197,201 @@ __device__ __forceinline__ int st_v0(unsigned long long w) { return (int)(w & 0x
 __device__ __forceinline__ int st_v1(unsigned long long w) { return (int)((w >> 31) & 0x7fffffffull); }
 
 template <bool G, int KIND>
-__global__ __launch_bounds__(kWG) void k_scan(DescArg<G> dg, Geom g, Arena a) {
+__device__ __forceinline__ void scan_chunk(const RunDesc& d, const Geom& g, const Arena& a, int64_t chunk) {
   constexpr int NCH = KIND == SCAN_SEEDS_FOLLOW ? 2 : 1;
   constexpr int SI = scan_items(G), SC = kWG * SI;
-  const RunDesc d = dg.get();
   const int64_t nel = KIND == SCAN_TILES ? (int64_t)d.n_events * g.L * g.tpl : (int64_t)d.n;
   const int64_t nout = nel + 1;  // the last output is the total
-  const int64_t nchunks = (nout + SC - 1) / SC;
   unsigned long long* status = a.scan_status + (KIND == SCAN_TILES ? 0 : a.cap_chunks);
-  int* ticket = &a.counters[KIND == SCAN_TILES ? C_TICKET_TILES : C_TICKET_SEEDS];
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
-  __shared__ int s_chunk;
   __shared__ int s_wsum[NCH][kWG / 64];
   __shared__ int s_prefix[NCH];
+  const int64_t base = chunk * SC + (int64_t)threadIdx.x * SI;
 
-  for (;;) {
-    if (threadIdx.x == 0) s_chunk = atomicAdd(ticket, 1);
-    __syncthreads();
-    const int64_t chunk = s_chunk;
-    __syncthreads();
-    if (chunk >= nchunks) break;
-    const int64_t base = chunk * SC + (int64_t)threadIdx.x * SI;
-
-    int v[NCH][SI];
-    if constexpr (KIND == SCAN_TILES) {
+  int v[NCH][SI];
+  if constexpr (KIND == SCAN_TILES) {
+    if (base + SI <= nel) {
+      const int4* p = reinterpret_cast<const int4*>(a.tile_start + base);
+#pragma unroll
+      for (int q = 0; q < SI / 4; ++q) {
+        int4 w = p[q];
+        v[0][4 * q] = w.x; v[0][4 * q + 1] = w.y; v[0][4 * q + 2] = w.z; v[0][4 * q + 3] = w.w;
+      }
+    } else {
+#pragma unroll
+      for (int i = 0; i < SI; ++i) v[0][i] = base + i < nel ? a.tile_start[base + i] : 0;
+    }
+  } else {
+    // channel 0: the seeds of bitmap word w at element 32 w, zero elsewhere,
+    // so that the prefix at 32 w counts the seeds before word w
+    static_assert(SI % 32 == 0 || 32 % SI == 0, "a thread's elements hold whole words or none");
+    const int64_t nw = seed_words(d.n);
+    // the bitmap words of this thread's elements, loaded once
+    constexpr int NW = (SI + 31) / 32;
+    unsigned wv[NW];
+#pragma unroll
+    for (int k = 0; k < NW; ++k) wv[k] = (base >> 5) + k < nw ? a.seedbits[(base >> 5) + k] : 0u;
+#pragma unroll
+    for (int i = 0; i < SI; ++i) {
+      const int64_t e = base + i;
+      v[0][i] = (e & 31) == 0 ? __popc(wv[(e >> 5) - (base >> 5)]) : 0;
+    }
+    // the follower counts are loaded before the flag stores below, which
+    // could alias them as far as the compiler knows
+    if constexpr (NCH == 2) {
       if (base + SI <= nel) {
-        const int4* p = reinterpret_cast<const int4*>(a.tile_start + base);
+        const int4* p = reinterpret_cast<const int4*>(a.fstart + base);
 #pragma unroll
         for (int q = 0; q < SI / 4; ++q) {
           int4 w = p[q];
-          v[0][4 * q] = w.x; v[0][4 * q + 1] = w.y; v[0][4 * q + 2] = w.z; v[0][4 * q + 3] = w.w;
+          v[1][4 * q] = w.x; v[1][4 * q + 1] = w.y; v[1][4 * q + 2] = w.z; v[1][4 * q + 3] = w.w;
         }
       } else {
 #pragma unroll
-        for (int i = 0; i < SI; ++i) v[0][i] = base + i < nel ? a.tile_start[base + i] : 0;
+        for (int i = 0; i < SI; ++i) v[1][i] = base + i < nel ? a.fstart[base + i] : 0;
       }
+    }
+    // the caller-order seed flags, expanded from the bitmap 16 at a time
+    // (one bit per hit -> one byte per hit), in coalesced stores
+    static_assert(SI % 16 == 0, "flags are written 16 at a time");
+#pragma unroll
+    for (int q = 0; q < SI; q += 16) {
+      const int64_t e0 = base + q;
+      if (e0 >= nel) break;
+      const unsigned w = (wv[(e0 >> 5) - (base >> 5)] >> (e0 & 31)) & 0xffffu;
+      unsigned b4[4];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) b4[k] = (((w >> (4 * k)) & 0xfu) * 0x00204081u) & 0x01010101u;
+      uint8_t* dst = d.is_seed + e0;
+      if (e0 + 16 <= nel && ((uintptr_t)dst & 15u) == 0) {
+        *reinterpret_cast<uint4*>(dst) = make_uint4(b4[0], b4[1], b4[2], b4[3]);
+      } else {
+        for (int k = 0; k < 16 && e0 + k < nel; ++k) dst[k] = (uint8_t)((w >> k) & 1u);
+      }
+    }
+  }
+  // thread-local exclusive prefix
+  int tsum[NCH];
+#pragma unroll
+  for (int c = 0; c < NCH; ++c) {
+    int acc = 0;
+#pragma unroll
+    for (int i = 0; i < SI; ++i) {
+      int t = v[c][i];
+      v[c][i] = acc;
+      acc += t;
+    }
+    tsum[c] = acc;
+  }
+  int texcl[NCH];
+#pragma unroll
+  for (int c = 0; c < NCH; ++c) {
+    int incl = wave_incl_scan(tsum[c], lane);
+    texcl[c] = incl - tsum[c];
+    if (lane == 63) s_wsum[c][wave] = incl;
+  }
+  __syncthreads();
+  int agg[NCH];
+  int wbase[NCH];
+#pragma unroll
+  for (int c = 0; c < NCH; ++c) {
+    int acc = 0;
+    wbase[c] = 0;
+#pragma unroll
+    for (int w = 0; w < kWG / 64; ++w) {
+      if (w == wave) wbase[c] = acc;
+      acc += s_wsum[c][w];
+    }
+    agg[c] = acc;
+  }
+  // look-back by wave 0
+  if (wave == 0) {
+    int run[NCH];
+#pragma unroll
+    for (int c = 0; c < NCH; ++c) run[c] = 0;
+    if (chunk == 0) {
+      if (lane == 0)
+        __hip_atomic_store(&status[0], st_pack(2, agg[0], NCH == 2 ? agg[NCH - 1] : 0), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
     } else {
-      // channel 0: the seeds of bitmap word w at element 32 w, zero elsewhere,
-      // so that the prefix at 32 w counts the seeds before word w
-      static_assert(SI % 32 == 0 || 32 % SI == 0, "a thread's elements hold whole words or none");
-      const int64_t nw = seed_words(d.n);
-      // the bitmap words of this thread's elements, loaded once
-      constexpr int NW = (SI + 31) / 32;
-      unsigned wv[NW];
-#pragma unroll
-      for (int k = 0; k < NW; ++k) wv[k] = (base >> 5) + k < nw ? a.seedbits[(base >> 5) + k] : 0u;
-#pragma unroll
-      for (int i = 0; i < SI; ++i) {
-        const int64_t e = base + i;
-        v[0][i] = (e & 31) == 0 ? __popc(wv[(e >> 5) - (base >> 5)]) : 0;
-      }
-      // the follower counts are loaded before the flag stores below, which
-      // could alias them as far as the compiler knows
-      if constexpr (NCH == 2) {
-        if (base + SI <= nel) {
-          const int4* p = reinterpret_cast<const int4*>(a.fstart + base);
-#pragma unroll
-          for (int q = 0; q < SI / 4; ++q) {
-            int4 w = p[q];
-            v[1][4 * q] = w.x; v[1][4 * q + 1] = w.y; v[1][4 * q + 2] = w.z; v[1][4 * q + 3] = w.w;
-          }
-        } else {
-#pragma unroll
-          for (int i = 0; i < SI; ++i) v[1][i] = base + i < nel ? a.fstart[base + i] : 0;
+      if (lane == 0)
+        __hip_atomic_store(&status[chunk], st_pack(1, agg[0], NCH == 2 ? agg[NCH - 1] : 0), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+      int64_t look = chunk - 1;
+      for (;;) {
+        const int64_t j = look - lane;
+        unsigned long long w = j >= 0 ? __hip_atomic_load(&status[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
+                                      : st_pack(2, 0, 0);
+        while (__any(st_flag(w) == 0)) {
+          if (st_flag(w) == 0)
+            w = __hip_atomic_load(&status[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
+        const unsigned long long incl_mask = __ballot(st_flag(w) == 2);
+        const int stop = incl_mask ? __ffsll((long long)incl_mask) - 1 : 64;
+        const bool take = lane <= stop;
+        run[0] += wave_sum(take ? st_v0(w) : 0);
+        if constexpr (NCH == 2) run[1] += wave_sum(take ? st_v1(w) : 0);
+        if (incl_mask) break;
+        look -= 64;
       }
-      // the caller-order seed flags, expanded from the bitmap 16 at a time
-      // (one bit per hit -> one byte per hit), in coalesced stores
-      static_assert(SI % 16 == 0, "flags are written 16 at a time");
-#pragma unroll
-      for (int q = 0; q < SI; q += 16) {
-        const int64_t e0 = base + q;
-        if (e0 >= nel) break;
-        const unsigned w = (wv[(e0 >> 5) - (base >> 5)] >> (e0 & 31)) & 0xffffu;
-        unsigned b4[4];
-#pragma unroll
-        for (int k = 0; k < 4; ++k) b4[k] = (((w >> (4 * k)) & 0xfu) * 0x00204081u) & 0x01010101u;
-        uint8_t* dst = d.is_seed + e0;
-        if (e0 + 16 <= nel && ((uintptr_t)dst & 15u) == 0) {
-          *reinterpret_cast<uint4*>(dst) = make_uint4(b4[0], b4[1], b4[2], b4[3]);
-        } else {
-          for (int k = 0; k < 16 && e0 + k < nel; ++k) dst[k] = (uint8_t)((w >> k) & 1u);
-        }
-      }
+      if (lane == 0)
+        __hip_atomic_store(&status[chunk],
+                           st_pack(2, run[0] + agg[0], NCH == 2 ? run[NCH - 1] + agg[NCH - 1] : 0),
+                           __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    // thread-local exclusive prefix
-    int tsum[NCH];
+    if (lane == 0) {
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      int acc = 0;
-#pragma unroll
-      for (int i = 0; i < SI; ++i) {
-        int t = v[c][i];
-        v[c][i] = acc;
-        acc += t;
-      }
-      tsum[c] = acc;
+      for (int c = 0; c < NCH; ++c) s_prefix[c] = run[c];
     }
-    int texcl[NCH];
+  }
+  __syncthreads();
+  // outputs
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      int incl = wave_incl_scan(tsum[c], lane);
-      texcl[c] = incl - tsum[c];
-      if (lane == 63) s_wsum[c][wave] = incl;
+  for (int c = 0; c < NCH; ++c) {
+    const int off = s_prefix[c] + wbase[c] + texcl[c];
+    if (KIND != SCAN_TILES && c == 0) {  // one count per bitmap word
+#pragma unroll
+      for (int i = 0; i < SI; i += 32)
+        if (base + i < nout && ((base + i) & 31) == 0) a.seed_wrank[(base + i) >> 5] = off + v[c][i];
+      continue;
     }
+    int* out = KIND == SCAN_TILES ? a.tile_start : a.fstart;
+    if (base + SI <= nout) {
+      int4* p = reinterpret_cast<int4*>(out + base);
+#pragma unroll
+      for (int q = 0; q < SI / 4; ++q)
+        p[q] = make_int4(off + v[c][4 * q], off + v[c][4 * q + 1], off + v[c][4 * q + 2], off + v[c][4 * q + 3]);
+    } else {
+#pragma unroll
+      for (int i = 0; i < SI; ++i)
+        if (base + i < nout) out[base + i] = off + v[c][i];
+    }
+  }
+  __syncthreads();
+}
+
+template <bool G, int KIND>
+__host__ __device__ __forceinline__ int scan_chunks(const RunDesc& d, const Geom& g) {
+  constexpr int SC = kWG * scan_items(G);
+  const int64_t nel = KIND == SCAN_TILES ? (int64_t)d.n_events * g.L * g.tpl : (int64_t)d.n;
+  return (int)((nel + SC) / SC);  // nel + 1 outputs
+}
+
+template <bool G, int KIND>
+__global__ __launch_bounds__(kWG) void k_scan(DescArg<G> dg, Geom g, Arena a) {
+  if (by_units(g, a)) return;  // done unit by unit
+  const RunDesc d = dg.get();
+  const int nchunks = scan_chunks<G, KIND>(d, g);
+  int* ticket = &a.counters[KIND == SCAN_TILES ? C_TICKET_TILES : C_TICKET_SEEDS];
+  __shared__ int s_chunk;
+  for (;;) {
+    if (threadIdx.x == 0) s_chunk = atomicAdd(ticket, 1);
     __syncthreads();
-    int agg[NCH];
-    int wbase[NCH];
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      int acc = 0;
-      wbase[c] = 0;
-#pragma unroll
-      for (int w = 0; w < kWG / 64; ++w) {
-        if (w == wave) wbase[c] = acc;
-        acc += s_wsum[c][w];
-      }
-      agg[c] = acc;
-    }
-    // look-back by wave 0
-    if (wave == 0) {
-      int run[NCH];
-#pragma unroll
-      for (int c = 0; c < NCH; ++c) run[c] = 0;
-      if (chunk == 0) {
-        if (lane == 0)
-          __hip_atomic_store(&status[0], st_pack(2, agg[0], NCH == 2 ? agg[NCH - 1] : 0), __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_AGENT);
-      } else {
-        if (lane == 0)
-          __hip_atomic_store(&status[chunk], st_pack(1, agg[0], NCH == 2 ? agg[NCH - 1] : 0), __ATOMIC_RELAXED,
-                             __HIP_MEMORY_SCOPE_AGENT);
-        int64_t look = chunk - 1;
-        for (;;) {
-          const int64_t j = look - lane;
-          unsigned long long w = j >= 0 ? __hip_atomic_load(&status[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)
-                                        : st_pack(2, 0, 0);
-          while (__any(st_flag(w) == 0)) {
-            if (st_flag(w) == 0)
-              w = __hip_atomic_load(&status[j], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-          }
-          const unsigned long long incl_mask = __ballot(st_flag(w) == 2);
-          const int stop = incl_mask ? __ffsll((long long)incl_mask) - 1 : 64;
-          const bool take = lane <= stop;
-          run[0] += wave_sum(take ? st_v0(w) : 0);
-          if constexpr (NCH == 2) run[1] += wave_sum(take ? st_v1(w) : 0);
-          if (incl_mask) break;
-          look -= 64;
-        }
-        if (lane == 0)
-          __hip_atomic_store(&status[chunk],
-                             st_pack(2, run[0] + agg[0], NCH == 2 ? run[NCH - 1] + agg[NCH - 1] : 0),
-                             __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      }
-      if (lane == 0) {
-#pragma unroll
-        for (int c = 0; c < NCH; ++c) s_prefix[c] = run[c];
-      }
-    }
+    const int chunk = s_chunk;
     __syncthreads();
-    // outputs
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      const int off = s_prefix[c] + wbase[c] + texcl[c];
-      if (KIND != SCAN_TILES && c == 0) {  // one count per bitmap word
-#pragma unroll
-        for (int i = 0; i < SI; i += 32)
-          if (base + i < nout && ((base + i) & 31) == 0) a.seed_wrank[(base + i) >> 5] = off + v[c][i];
-        continue;
-      }
-      int* out = KIND == SCAN_TILES ? a.tile_start : a.fstart;
-      if (base + SI <= nout) {
-        int4* p = reinterpret_cast<int4*>(out + base);
-#pragma unroll
-        for (int q = 0; q < SI / 4; ++q)
-          p[q] = make_int4(off + v[c][4 * q], off + v[c][4 * q + 1], off + v[c][4 * q + 2], off + v[c][4 * q + 3]);
-      } else {
-#pragma unroll
-        for (int i = 0; i < SI; ++i)
-          if (base + i < nout) out[base + i] = off + v[c][i];
-      }
-    }
-    __syncthreads();
+    if (chunk >= nchunks) break;
+    scan_chunk<G, KIND>(d, g, a, chunk);
   }
 }
 
@@ -1468,10 +1320,6 @@ __device__ __forceinline__ void nh_consider(NhBest& b, float d2, unsigned ordj, 
 // like the caller index, so the (rho, index) and (d2, index) keys compare as
 // before, and the winner's LDS position comes back out of its key: the scan
 // tracks no position of its own.
-constexpr int kPosBits = 11;
-constexpr unsigned kPosMask = (1u << kPosBits) - 1u;
-constexpr int kPackedEventMax = 1 << (32 - kPosBits);  // hits per event
-static_assert(kMaxLdsCap <= (1 << kPosBits), "an LDS position must fit the packed index word");
 __device__ __forceinline__ unsigned nh_pack(int h, int ev_first, int p) {
   return ((unsigned)(h - ev_first) << kPosBits) | (unsigned)p;
 }
@@ -1499,8 +1347,12 @@ __device__ __forceinline__ void nh_reduce(NhBest& b, int tpq) {
 
 // Writes the decision for the hit in `slot` with nearest-higher `b` (b.p
 // already converted to a slot index, or -1).
-__device__ __forceinline__ void decide_and_store(const Geom& g, const Arena& a, const RunDesc& d, int slot, int hi,
-                                                 float ri, const NhBest& b, int ev_first) {
+//
+// The unit path numbers seeds and builds follower lists unit by unit
+// afterwards. It needs only each unit's counts of both here: the workgroup
+// collects them in `counts` (the hits it decides together are in one unit).
+__device__ __forceinline__ void decide_and_store(const Geom& g, const Arena& a, const RunDesc& d, int* counts, int slot,
+                                                 int hi, float ri, const NhBest& b, int ev_first) {
   const bool has = b.p >= 0;
   const float d2 = has ? b.d2() : __int_as_float(0x7f800000);
   const bool seed = ri > g.rho_c && d2 > g.dcs2;
@@ -1508,8 +1360,17 @@ __device__ __forceinline__ void decide_and_store(const Geom& g, const Arena& a, 
   const bool follower = !seed && !outlier && has;
   a.parent[slot] = follower ? b.p : slot;
   a.flags[slot] = (uint8_t)((seed ? F_SEED : 0) | (outlier ? F_OUTLIER : 0) | (follower ? F_FOLLOWER : 0));
-  if (seed) atomicOr(&a.seedbits[hi >> 5], 1u << (hi & 31));
-  if (follower && builds_lists(g)) a.frank[slot] = atomicAdd(&a.fstart[b.h()], 1);
+  if (g.units) {
+    const unsigned long long ms = __builtin_amdgcn_ballot_w64(seed), mf = __builtin_amdgcn_ballot_w64(follower);
+    const unsigned long long on = __builtin_amdgcn_ballot_w64(true);
+    if (((int)threadIdx.x & 63) == __ffsll((long long)on) - 1) {
+      atomicAdd(&counts[0], __popcll(ms));
+      atomicAdd(&counts[1], __popcll(mf));
+    }
+  } else {
+    if (seed) atomicOr(&a.seedbits[hi >> 5], 1u << (hi & 31));
+    if (follower && builds_lists(g)) a.frank[slot] = atomicAdd(&a.fstart[b.h()], 1);
+  }
   if (g.flags & 2u) {
     a.nh_out[hi] = has ? b.h() - ev_first : -1;
     a.d2_out[hi] = d2;
@@ -1572,7 +1433,7 @@ __device__ __forceinline__ void nh_global_scan(const Geom& g, const Arena& a, in
 template <bool STRICT>
 __device__ __forceinline__ bool nh_staged(const Geom& g, const Arena& a, const RunDesc& d, const Region& R, const RegionLds& L,
                           float4* rec, unsigned short* queue, unsigned char* prow, unsigned short* coreq, int* s_qn,
-                          int ev_first) {
+                          int* s_counts, int ev_first) {
   const int per_row = R.rw + 1;
   const int64_t ubase = (int64_t)R.unit * g.tpl;
   // the region row of every staged position (it gives the staging loads
@@ -1635,7 +1496,7 @@ __device__ __forceinline__ bool nh_staged(const Geom& g, const Arena& a, const R
         nh_unpack(b, k0, ev_first);
         if (b.p >= 0) {
           b.p = slot_of(L, prow[b.p], b.p);
-          decide_and_store(g, a, d, slot_of(L, row, p), nh_unpack_h(zi, ev_first), ord_inv(ordi), b, ev_first);
+          decide_and_store(g, a, d, s_counts, slot_of(L, row, p), nh_unpack_h(zi, ev_first), ord_inv(ordi), b, ev_first);
           done = true;
         }
       }
@@ -1679,7 +1540,7 @@ __device__ __forceinline__ bool nh_staged(const Geom& g, const Arena& a, const R
         b.p = slot_of(L, prow[b.p], b.p);
       else if (b.p <= -2)
         b.p = -2 - b.p;
-      decide_and_store(g, a, d, slot, (int)hi, ord_inv(ordi), b, ev_first);
+      decide_and_store(g, a, d, s_counts, slot, (int)hi, ord_inv(ordi), b, ev_first);
     }
   }
   return true;
@@ -1687,7 +1548,7 @@ __device__ __forceinline__ bool nh_staged(const Geom& g, const Arena& a, const R
 
 template <bool STRICT>
 __device__ __forceinline__ void nh_global_region(const Geom& g, const Arena& a, const RunDesc& d, const Region& R,
-                                 const RegionLds& L, int ev_first) {
+                                 const RegionLds& L, int* s_counts, int ev_first) {
   const int64_t ubase = (int64_t)R.unit * g.tpl;
   const int nq = L.core_lo[R.ch];
   const int tpq = g.tpq;
@@ -1712,7 +1573,7 @@ __device__ __forceinline__ void nh_global_region(const Geom& g, const Arena& a, 
     nh_reduce(b, tpq);
     if (active && sub == 0) {
       if (b.p <= -2) b.p = -2 - b.p;
-      decide_and_store(g, a, d, slot, (int)hi, a.rho[slot], b, ev_first);
+      decide_and_store(g, a, d, s_counts, slot, (int)hi, a.rho[slot], b, ev_first);
     }
   }
 }
@@ -1720,8 +1581,8 @@ __device__ __forceinline__ void nh_global_region(const Geom& g, const Arena& a, 
 template <bool STRICT>
 __device__ __forceinline__ void nh_item(const Geom& g, const Arena& a, const RunDesc& d, int item, RegionLds& L,
                                         float4* rec, unsigned short* queue, unsigned char* prow, unsigned short* coreq,
-                                        int* s_qn, unsigned short* s_stack) {
-  int unit, tx0, ty0, tx1, ty1;
+                                        int* s_qn, int* s_counts, unsigned short* s_stack, int& unit) {
+  int tx0, ty0, tx1, ty1;
   item_block(g, item, unit, tx0, ty0, tx1, ty1);
   const int e = unit / g.L;
   const int ev_first = event_first_hit(a, d, e);
@@ -1739,8 +1600,8 @@ __device__ __forceinline__ void nh_item(const Geom& g, const Arena& a, const Run
       } else if (R.total > g.lds_cap) {
         B.split();
         continue;
-      } else if (!nh_staged<STRICT>(g, a, d, R, L, rec, queue, prow, coreq, s_qn, ev_first)) {
-        nh_global_region<STRICT>(g, a, d, R, L, ev_first);
+      } else if (!nh_staged<STRICT>(g, a, d, R, L, rec, queue, prow, coreq, s_qn, s_counts, ev_first)) {
+        nh_global_region<STRICT>(g, a, d, R, L, s_counts, ev_first);
       }
     }
     more = B.next();
@@ -1751,11 +1612,15 @@ __device__ __forceinline__ void nh_item(const Geom& g, const Arena& a, const Run
 // memory, with the decision.
 template <bool G, bool STRICT>
 __global__ __launch_bounds__(kWG) void k_nh_spill(DescArg<G> dg, Geom g, Arena a) {
+  __shared__ int s_counts[2];
+  g.units = by_units(g, a);
   const RunDesc d = dg.get();
   const int nch = a.counters[C_SPILL_NH];
   const int tpq = g.tpq;
   const int sub = threadIdx.x & (tpq - 1);
   for (int i = blockIdx.x; i < nch; i += gridDim.x) {  // uniform per workgroup: the shuffles below
+    if (threadIdx.x < 2) s_counts[threadIdx.x] = 0;
+    __syncthreads();
     const int64_t t = a.key[i];
     const int slot = a.rank[i] + (int)threadIdx.x / tpq;
     const bool active = slot < a.tile_start[t + 1];
@@ -1772,8 +1637,11 @@ __global__ __launch_bounds__(kWG) void k_nh_spill(DescArg<G> dg, Geom g, Arena a
     nh_reduce(b, tpq);
     if (active && sub == 0) {
       if (b.p <= -2) b.p = -2 - b.p;
-      decide_and_store(g, a, d, slot, (int)hi, a.rho[slot], b, ev_first);
+      decide_and_store(g, a, d, s_counts, slot, (int)hi, a.rho[slot], b, ev_first);
     }
+    __syncthreads();
+    if (g.units && threadIdx.x < 2 && s_counts[threadIdx.x])
+      atomicAdd(&unit_counts(a, d, g)[2 * (int)(t / g.tpl) + (int)threadIdx.x], s_counts[threadIdx.x]);
   }
 }
 
@@ -1782,6 +1650,9 @@ __global__ __launch_bounds__(kWG) void k_nh_spill(DescArg<G> dg, Geom g, Arena a
 // runs 11% faster than at seven waves.
 template <bool G, bool STRICT>
 __global__ __launch_bounds__(kWG, 8) void k_nearest_higher(DescArg<G> dg, Geom g, Arena a) {
+  __shared__ int s_counts[2];
+  g.units = by_units(g, a);  // read once; the search functions see the answer
+  if (threadIdx.x < 2) s_counts[threadIdx.x] = 0;  // barriers follow before the first decision
   const RunDesc d = dg.get();
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int s_rows[kRowMetaInts];
@@ -1796,116 +1667,26 @@ __global__ __launch_bounds__(kWG, 8) void k_nearest_higher(DescArg<G> dg, Geom g
   const int n_items = d.n_events * g.L * g.bpu;
   ItemSched st{0, G ? xcc_id() : 0};
   for (int item; (item = next_item<G>(st, n_items, &a.counters[C_QUEUE_NH], &s_item)) >= 0;)
-    nh_item<STRICT>(g, a, d, item, L, rec, queue, prow, coreq, &s_qn, s_stack);
+  {
+    int unit;
+    nh_item<STRICT>(g, a, d, item, L, rec, queue, prow, coreq, &s_qn, s_counts, s_stack, unit);
+    if (g.units) {
+      __syncthreads();
+      if (threadIdx.x < 2) {
+        const int c = s_counts[threadIdx.x];
+        s_counts[threadIdx.x] = 0;
+        if (c) atomicAdd(&unit_counts(a, d, g)[2 * unit + (int)threadIdx.x], c);
+      }
+    }
+  }
 }
 
-// ---------------------------------------------------------------------------
-// Labels: follow the follower -> nearest-higher links to the root (pointer
-// jumping with path compression; concurrent updates only ever store an
-// ancestor, so every read is an ancestor and every chase ends at the root).
-// A root that is a seed gives its seed number within the event; any other
-// root (outlier, orphan) gives -1. Also places follower-list entries.
-// ---------------------------------------------------------------------------
 template <bool G>
 __global__ __launch_bounds__(kWG) void k_label(DescArg<G> dg, Geom g, Arena a) {
+  constexpr int U = G ? kBatchU : kPlaceU;
+  __shared__ LabelChunk<kWG * U> S;
   const RunDesc d = dg.get();
-  const bool fol = builds_lists(g);
-  constexpr int U = G ? kBatchU : kPlaceU;  // hits per lane per step, their chases interleaved
-  constexpr int C = kWG * U;  // slots per chunk
-  // the chunk's parent, caller index and flags, staged in LDS: a nearest-higher
-  // lies within d_m, so most links stay inside the chunk. A staged parent may
-  // be older than a compression stored since; it is still an ancestor.
-  __shared__ int s_par[C];
-  __shared__ int s_hs[C];
-  __shared__ unsigned char s_fl[C];
-  __shared__ int s_ev[2];  // the chunk's event when it holds one event (else -1), its first hit
-  for (ChunkRun rn = xcd_run(d.n, C); rn.c < rn.end; rn.c += rn.step) {
-    const int c0 = rn.c * C;
-    if (threadIdx.x == 0) {
-      const int e0 = event_of_slot(g, a, d, c0);
-      const int e1 = event_of_slot(g, a, d, min(c0 + C, d.n) - 1);
-      s_ev[0] = e0 == e1 ? e0 : -1;
-      s_ev[1] = event_first_hit(a, d, e0);
-    }
-    const int sb = c0 + (int)threadIdx.x;
-    int s[U], p0[U], hsj[U], r[U], p[U];
-    unsigned f[U];
-    bool v[U];
-#pragma unroll
-    for (int j = 0; j < U; ++j) {
-      s[j] = sb + j * kWG;
-      v[j] = s[j] < d.n;
-      p0[j] = s[j];
-      hsj[j] = 0;
-      f[j] = 0;
-      if (v[j]) {
-        p0[j] = a.parent[s[j]];
-        f[j] = a.flags[s[j]];
-        hsj[j] = a.hs[s[j]];
-      }
-      s_par[s[j] - c0] = p0[j];
-      s_hs[s[j] - c0] = hsj[j];
-      s_fl[s[j] - c0] = (unsigned char)f[j];
-    }
-    __syncthreads();
-    auto staged = [&](int x) { return (unsigned)(x - c0) < (unsigned)C; };
-    // first hit of each hit's event, from its slot
-    const int ev1 = s_ev[0], first1 = s_ev[1];
-    int first[U];
-#pragma unroll
-    for (int j = 0; j < U; ++j)
-      first[j] = ev1 >= 0 || !v[j] ? first1 : event_first_hit(a, d, event_of_slot(g, a, d, s[j]));
-    if (fol) {
-      // entries are event-local already: the list sort then leaves lists of
-      // one entry alone. Every load of a lane comes before its first store
-      // (the stores could alias them as far as the compiler knows).
-      int at[U];
-#pragma unroll
-      for (int j = 0; j < U; ++j) {
-        at[j] = -1;
-        if (v[j] && (f[j] & F_FOLLOWER)) {
-          const int owner = staged(p0[j]) ? s_hs[p0[j] - c0] : a.hs[p0[j]];
-          at[j] = a.fstart[owner] + a.frank[s[j]];
-        }
-      }
-#pragma unroll
-      for (int j = 0; j < U; ++j)
-        if (at[j] >= 0) a.flist[at[j]] = hsj[j] - first[j];
-    }
-#pragma unroll
-    for (int j = 0; j < U; ++j) {
-      r[j] = s[j];
-      p[j] = p0[j];
-    }
-    for (;;) {
-      bool more = false;
-#pragma unroll
-      for (int j = 0; j < U; ++j) {
-        if (p[j] != r[j]) {
-          r[j] = p[j];
-          p[j] = staged(r[j]) ? s_par[r[j] - c0] : ld_relaxed(&a.parent[r[j]]);
-          more = true;
-        }
-      }
-      if (!more) break;
-    }
-    int lab[U];
-#pragma unroll
-    for (int j = 0; j < U; ++j) {
-      lab[j] = -1;
-      if (!v[j]) continue;
-      const bool in = staged(r[j]);
-      if ((in ? s_fl[r[j] - c0] : a.flags[r[j]]) & F_SEED)
-        lab[j] = seed_rank(a, in ? s_hs[r[j] - c0] : a.hs[r[j]]) - seed_rank(a, first[j]);
-    }
-#pragma unroll
-    for (int j = 0; j < U; ++j) {
-      if (!v[j]) continue;
-      if (r[j] != s[j] && r[j] != p0[j]) st_relaxed(&a.parent[s[j]], r[j]);
-      d.cluster_id[hsj[j]] = lab[j];
-    }
-    __syncthreads();  // the next chunk overwrites the staged arrays
-  }
+  for (ChunkRun r = xcd_run(d.n, stream_chunk(G)); r.c < r.end; r.c += r.step) label_chunk<kWG, U>(d, g, a, r.c * stream_chunk(G), d.n, S);
 }
 
 // ---------------------------------------------------------------------------
@@ -2019,80 +1800,84 @@ __global__ __launch_bounds__(kWG) void k_expand_dfs(DescArg<G> dg, Geom g, Arena
 constexpr int kShortList = 8;
 
 template <bool G>
-__global__ __launch_bounds__(kWG) void k_follow_sort(DescArg<G> dg, Geom g, Arena a) {
-  const RunDesc d = dg.get();
+__device__ __forceinline__ void follow_sort_chunk(const RunDesc& d, const Geom& g, const Arena& a, int chunk) {
   constexpr int U = kPlaceU;
-  for (ChunkRun rn = xcd_run(d.n, kWG * U); rn.c < rn.end; rn.c += rn.step) {
-    const int hb = rn.c * kWG * U + (int)threadIdx.x;
-    int b[U], end[U];
+  const int hb = chunk * kWG * U + (int)threadIdx.x;
+  int b[U], end[U];
 #pragma unroll
-    for (int j = 0; j < U; ++j) {
-      const int h = hb + j * kWG;
-      b[j] = 0;
-      end[j] = 0;
-      if (h < d.n) {
-        b[j] = a.fstart[h];
-        end[j] = a.fstart[h + 1];
-      }
-    }
-#pragma unroll
-    for (int j = 0; j < U; ++j) {
-      const int len = end[j] - b[j];
-      // nearly every wave holds only lists of up to four entries: then the
-      // whole wave takes the shorter network (a wave-uniform choice)
-      const bool four = __all(len <= 4);
-      if (len < (g.expand ? 1 : 2)) continue;
-      int off = 0;
-      if (g.expand) {
-        const int h = hb + j * kWG;
-        off = event_first_hit(a, d, d.event ? clampi(d.event[h] - d.event_base, 0, d.n_events - 1) : 0);
-      }
-      if (four) {
-        int v[4];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) v[i] = i < len ? a.flist[b[j] + i] : INT_MAX;
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-#pragma unroll
-          for (int i = r & 1; i + 1 < 4; i += 2) {
-            const int lo = min(v[i], v[i + 1]), hi = max(v[i], v[i + 1]);
-            v[i] = lo;
-            v[i + 1] = hi;
-          }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (i < len) a.flist[b[j] + i] = v[i] - off;
-        continue;
-      }
-      if (len <= kShortList) {
-        int v[kShortList];
-#pragma unroll
-        for (int i = 0; i < kShortList; ++i) v[i] = i < len ? a.flist[b[j] + i] : INT_MAX;
-#pragma unroll
-        for (int r = 0; r < kShortList; ++r)
-#pragma unroll
-          for (int i = r & 1; i + 1 < kShortList; i += 2) {
-            const int lo = min(v[i], v[i + 1]), hi = max(v[i], v[i + 1]);
-            v[i] = lo;
-            v[i + 1] = hi;
-          }
-#pragma unroll
-        for (int i = 0; i < kShortList; ++i)
-          if (i < len) a.flist[b[j] + i] = v[i] - off;
-        continue;
-      }
-      for (int i = b[j] + 1; i < end[j]; ++i) {
-        const int v = a.flist[i];
-        int k = i - 1;
-        while (k >= b[j] && a.flist[k] > v) {
-          a.flist[k + 1] = a.flist[k];
-          --k;
-        }
-        a.flist[k + 1] = v;
-      }
-      for (int i = b[j]; i < end[j]; ++i) a.flist[i] -= off;
+  for (int j = 0; j < U; ++j) {
+    const int h = hb + j * kWG;
+    b[j] = 0;
+    end[j] = 0;
+    if (h < d.n) {
+      b[j] = a.fstart[h];
+      end[j] = a.fstart[h + 1];
     }
   }
+#pragma unroll
+  for (int j = 0; j < U; ++j) {
+    const int len = end[j] - b[j];
+    // nearly every wave holds only lists of up to four entries: then the
+    // whole wave takes the shorter network (a wave-uniform choice)
+    const bool four = __all(len <= 4);
+    if (len < (g.expand ? 1 : 2)) continue;
+    int off = 0;
+    if (g.expand) {
+      const int h = hb + j * kWG;
+      off = event_first_hit(a, d, d.event ? clampi(d.event[h] - d.event_base, 0, d.n_events - 1) : 0);
+    }
+    if (four) {
+      int v[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = i < len ? a.flist[b[j] + i] : INT_MAX;
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int i = r & 1; i + 1 < 4; i += 2) {
+          const int lo = min(v[i], v[i + 1]), hi = max(v[i], v[i + 1]);
+          v[i] = lo;
+          v[i + 1] = hi;
+        }
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+        if (i < len) a.flist[b[j] + i] = v[i] - off;
+      continue;
+    }
+    if (len <= kShortList) {
+      int v[kShortList];
+#pragma unroll
+      for (int i = 0; i < kShortList; ++i) v[i] = i < len ? a.flist[b[j] + i] : INT_MAX;
+#pragma unroll
+      for (int r = 0; r < kShortList; ++r)
+#pragma unroll
+        for (int i = r & 1; i + 1 < kShortList; i += 2) {
+          const int lo = min(v[i], v[i + 1]), hi = max(v[i], v[i + 1]);
+          v[i] = lo;
+          v[i + 1] = hi;
+        }
+#pragma unroll
+      for (int i = 0; i < kShortList; ++i)
+        if (i < len) a.flist[b[j] + i] = v[i] - off;
+      continue;
+    }
+    for (int i = b[j] + 1; i < end[j]; ++i) {
+      const int v = a.flist[i];
+      int k = i - 1;
+      while (k >= b[j] && a.flist[k] > v) {
+        a.flist[k + 1] = a.flist[k];
+        --k;
+      }
+      a.flist[k + 1] = v;
+    }
+    for (int i = b[j]; i < end[j]; ++i) a.flist[i] -= off;
+  }
+}
+
+template <bool G>
+__global__ __launch_bounds__(kWG) void k_follow_sort(DescArg<G> dg, Geom g, Arena a) {
+  if (by_units(g, a)) return;  // done unit by unit
+  const RunDesc d = dg.get();
+  for (ChunkRun r = xcd_run(d.n, kHistChunk); r.c < r.end; r.c += r.step) follow_sort_chunk<G>(d, g, a, r.c);
 }
 
 // ---------------------------------------------------------------------------
@@ -2159,9 +1944,15 @@ static hipError_t launch_all(const Geom& g, const Arena& a, DescArg<G> dg, const
     if (ev) (void)hipEventRecord(ev[k++], s);
   };
   mark();
-  k_clear<G><<<g_clear, kWG, 0, s>>>(dg, g, a);
+  if (g.units)
+    launch_units<G>(g, a, dg, host_d, s);
+  else
+    k_clear<G><<<g_clear, kWG, 0, s>>>(dg, g, a);
   mark();
-  k_hist<G><<<stream_grid(cdiv(n, kPlaceU)), kWG, 0, s>>>(dg, g, a);
+  if (g.units)
+    launch_unit_sort<G>(g, a, dg, host_d, s);  // or the histogram
+  else
+    k_hist<G><<<stream_grid(cdiv(n, kPlaceU)), kWG, 0, s>>>(dg, g, a);
   mark();
   k_scan<G, SCAN_TILES><<<g_scan_t, kWG, 0, s>>>(dg, g, a);
   mark();
@@ -2203,7 +1994,9 @@ static hipError_t launch_all(const Geom& g, const Arena& a, DescArg<G> dg, const
   else
     k_scan<G, SCAN_SEEDS><<<g_scan_s, kWG, 0, s>>>(dg, g, a);
   mark();
-  if (g.expand) {
+  if (g.units) {
+    launch_unit_finish<G>(g, a, dg, host_d, s);  // or the labels
+  } else if (g.expand) {
     k_expand_init<G><<<stream_grid(cdiv(n, kPlaceU)), kWG, 0, s>>>(dg, g, a);
     const int g_dfs = G ? cfg.persist_blocks_stream : std::min(stream_grid(n), std::max(1, cfg.persist_blocks_stream));
     k_expand_dfs<G><<<g_dfs, kWG, 0, s>>>(dg, g, a);
