@@ -128,9 +128,9 @@ struct Arena {
                          //       (the depth-first expansion reuses both for each
                          //       follower's owner and its position in the owner's list)
                          //       (the unit path keeps its arrays at their ends)
-                         //       (the grid build keeps arrival-order hit ids and tiles
-                         //       in the rho and parent buffers until each tile is
-                         //       ordered by hit index)
+                         //       (the grid build keeps (hit id, tile) pairs in arrival
+                         //       order in the adjoining rho and parent buffers until
+                         //       each tile is ordered by hit index)
   int32_t* tile_start;   // [TT+1] tile counts, scanned in place into CSR offsets
   float* xs;             // [N]   slot order (tile CSR; hit index ascending within a tile);
                          //       after the nearest-higher stage, the depth-first
@@ -138,7 +138,7 @@ struct Arena {
   float* ys;
   float* es;
   int32_t* hs;           // [N]   slot -> caller (batch-global) hit index
-  float* rho;            // [N]   slot order
+  float* rho;            // [N]   slot order; its buffer and the parents' adjoin
   int32_t* parent;       // [N]   slot order: nearest-higher slot of a follower, else itself
   uint8_t* flags;        // [N]   slot order: F_SEED | F_OUTLIER | F_FOLLOWER
   uint32_t* seedbits;    // [N/32+2] caller order: one bit per hit, set for seeds

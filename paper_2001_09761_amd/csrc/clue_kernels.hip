@@ -71,8 +71,9 @@ __global__ __launch_bounds__(kWG) void k_hist(DescArg<G> dg, Geom g, Arena a) {
 
 // ---------------------------------------------------------------------------
 // k_scatter: hit h's id and tile go to slot tile_start[tile] + rank (arrival
-// order within a tile), kept in the rho and parent buffers, which are free
-// until the density stage.
+// order within a tile) as one eight-byte pair, so that hits in no order touch one
+// line each, not two. The pairs lie in the rho and parent buffers, which are free
+// until the density stage and adjoin.
 // k_place: slot by slot, each hit counts the ids of its tile that are smaller
 // than its own and writes its record at that position, so every tile of the
 // CSR lists its hits in ascending hit index. Neighbouring slots share their
@@ -80,7 +81,7 @@ __global__ __launch_bounds__(kWG) void k_hist(DescArg<G> dg, Geom g, Arena a) {
 // ---------------------------------------------------------------------------
 template <bool G>
 __device__ __forceinline__ void scatter_chunk(const RunDesc& d, const Geom& g, const Arena& a, int chunk) {
-  int* ids = reinterpret_cast<int*>(a.rho);
+  int2* const pairs = reinterpret_cast<int2*>(a.rho);
   constexpr int U = G ? kBatchU : kPlaceU;
   const int h0 = chunk * kWG * U + (int)threadIdx.x;
   int t[U], r[U];
@@ -97,8 +98,7 @@ __device__ __forceinline__ void scatter_chunk(const RunDesc& d, const Geom& g, c
   for (int j = 0; j < U; ++j) {
     if (t[j] >= 0) {
       const int s = a.tile_start[t[j]] + r[j];
-      ids[s] = h0 + j * kWG;
-      a.parent[s] = t[j];
+      pairs[s] = make_int2(h0 + j * kWG, t[j]);
     }
   }
 }
@@ -112,7 +112,7 @@ __global__ __launch_bounds__(kWG) void k_scatter(DescArg<G> dg, Geom g, Arena a)
 
 template <bool G>
 __device__ __forceinline__ void place_chunk(const RunDesc& d, const Geom& g, const Arena& a, int chunk) {
-  const int* ids = reinterpret_cast<const int*>(a.rho);
+  const int2* const pairs = reinterpret_cast<const int2*>(a.rho);
   constexpr int U = G ? kBatchU : kPlaceU;
   constexpr int C = kWG * U;  // slots per chunk
   // the chunk's arrival-order ids in LDS: a hit's tile mostly lies inside
@@ -120,10 +120,13 @@ __device__ __forceinline__ void place_chunk(const RunDesc& d, const Geom& g, con
   __shared__ int s_ids[C];
   const int c0 = chunk * C;
   const int c1 = min(c0 + C, d.n);
+  int tile[U];
 #pragma unroll
   for (int j = 0; j < U; ++j) {
     const int sl = c0 + (int)threadIdx.x + j * kWG;
-    s_ids[sl - c0] = sl < d.n ? ids[sl] : 0;
+    const int2 p = pairs[min(sl, d.n - 1)];
+    s_ids[sl - c0] = p.x;
+    tile[j] = p.y;
   }
   __syncthreads();
   // slots in groups of four: a group's loads are all issued before its
@@ -139,7 +142,7 @@ __device__ __forceinline__ void place_chunk(const RunDesc& d, const Geom& g, con
       hv[k] = -1;
       if (sl < d.n) {
         const int h = s_ids[sl - c0];
-        const int t = a.parent[sl];
+        const int t = tile[j0 + k];
         hv[k] = h;
         xv[k] = d.x[h];
         yv[k] = d.y[h];
@@ -155,12 +158,12 @@ __device__ __forceinline__ void place_chunk(const RunDesc& d, const Geom& g, con
       // the tile [s0, s1) in three parts: before the chunk, in it, after it
       const int m0 = min(max(s0, c0), s1), m1 = max(min(s1, c1), m0);
       int rk = 0;
-      for (int c = s0; c < m0; ++c) rk += ids[c] < h;
+      for (int c = s0; c < m0; ++c) rk += pairs[c].x < h;
       int c = m0;
       for (; c + 3 < m1; c += 4)
         rk += (s_ids[c - c0] < h) + (s_ids[c + 1 - c0] < h) + (s_ids[c + 2 - c0] < h) + (s_ids[c + 3 - c0] < h);
       for (; c < m1; ++c) rk += s_ids[c - c0] < h;
-      for (c = m1; c < s1; ++c) rk += ids[c] < h;
+      for (c = m1; c < s1; ++c) rk += pairs[c].x < h;
       const int slot = s0 + rk;
       a.xs[slot] = xv[k];
       a.ys[slot] = yv[k];
