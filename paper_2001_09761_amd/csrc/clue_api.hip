@@ -529,6 +529,10 @@ static int validate_inputs(clue_ctx* c, const RunDesc& d, hipStream_t s) {
   return CLUE_OK;
 }
 
+constexpr int64_t kSizedMaxHits = 1 << 22;   // hits, and work items, of the largest batch that
+constexpr int64_t kSizedMaxItems = 1 << 16;  // is run by launches sized to it
+constexpr int64_t kPlainCapHits = 1 << 21;   // ... and hits of the largest with the plain form's LDS cap
+
 static int run_common(clue_ctx* c, int64_t n, int32_t n_events, int32_t event_base, const int32_t* event,
                       const float* x, const float* y, const int32_t* layer, const float* energy, int32_t* cid,
                       uint8_t* seed, void* stream, bool batched) {
@@ -544,10 +548,18 @@ static int run_common(clue_ctx* c, int64_t n, int32_t n_events, int32_t event_ba
   HIP_TRY(c, hipSetDevice(c->device));
   hipStream_t s = (hipStream_t)stream;
   RunDesc d{};
-  if (!batched) {
-    c->g_plain = ctx_geom(c, n, 1);
+  // Launches sized to the run, as a single event's, or the captured graph's
+  // persistent kernels. The latter save launches and keep each XCD's items
+  // together; the former fit their chunks and their block to the run. One event of
+  // 620,000 hits in a batch takes 197 us by the graph and 174 us by sized
+  // launches, 4M hits 417 and 400 us, 8.9M hits 938 and 953 us (and so do 1.9M hits
+  // spread over 160,000 items, 1.82 and 1.84 ms, hence the second bound).
+  const Geom gr = ctx_geom(c, n, n_events);
+  const bool sized = !batched || (n <= kSizedMaxHits && (int64_t)n_events * gr.L * gr.bpu <= kSizedMaxItems);
+  if (sized) {
+    c->g_plain = gr;
     // the plain form may stage a different number of hits per work item
-    if (c->plain_cap > 0) c->g_plain.lds_cap = c->plain_cap;
+    if (c->plain_cap > 0 && n <= kPlainCapHits) c->g_plain.lds_cap = c->plain_cap;
   }
   d.n = (int32_t)n;
   d.n_events = n_events;
@@ -566,10 +578,10 @@ static int run_common(clue_ctx* c, int64_t n, int32_t n_events, int32_t event_ba
   hipEvent_t* ev = c->timing ? c->ev : nullptr;
   if (!c->tuned && n <= kDirectMax) {
     HIP_TRY(c, launch_direct(c->g, c->a, d, s, ev));
-  } else if (!batched) {
+  } else if (sized) {
     LaunchCfg cfg = c->cfg;
     cfg.graph_mode = false;
-    c->g_plain.units = units_grid(c->g_plain, n, n);
+    c->g_plain.units = units_grid(c->g_plain, batched ? 0 : n, n);
     HIP_TRY(c, launch_pipeline(c->g_plain, c->a, d, cfg, s, ev));
   } else {
     HIP_TRY(c, launch_set_desc(d, c->a.desc, s));

@@ -140,3 +140,23 @@ def test_long_chain_and_one_owner():
     star = dict(x=np.full(n, 30.0, np.float32), y=np.full(n, 30.0, np.float32), layer=np.ones(n, np.int32),
                 energy=np.ones(n, np.float32))
     assert_parity(gpu_run(star, p), _ref(star, p), where="coincident hits")
+
+
+@pytest.mark.parametrize("tuning", [dict(), dict(lds_cap=64), dict(density_quads=2), dict(density_quads=3, tile_size=5.0),
+                                    dict(expansion=2), dict(tile_size=2.5, nh_first_radius=0.0)])
+@pytest.mark.parametrize("order", ["grouped", "shuffled"])
+def test_small_runs_of_many_items_by_the_graph(tuning, order):
+    """Batches of up to 4M hits run by sized launches unless they have over
+    65,536 work items: here 160 events of 3 layers in one-tile blocks, so that the
+    captured graph's persistent kernels meet empty events, units of one hit,
+    crowded tiles (the spill queues at the low cap) and hits out of order."""
+    sizes = [[30 + 7 * (i % 5), i % 3, 100] if i % 11 else [0, 0, 0] for i in range(160)]
+    sizes[7] = [900, 500, 1025]
+    ids = list(range(160))
+    b = _batch(sizes, ids, 160)
+    if order == "shuffled":
+        q = np.argsort(b["event"] + 0.9 * np.random.default_rng(1).random(b["x"].size), kind="stable")
+        b = {k: (v[q] if isinstance(v, np.ndarray) else v) for k, v in b.items()}
+    p = dict(P, n_layers=3)
+    t = dict(dict(block_x=1, block_y=1, tile_size=4.03125), **tuning)
+    assert_parity(gpu_run(b, p, batched=True, n_events=160, tuning=t), _ref(b, p), where=f"{tuning} {order}")
