@@ -426,7 +426,8 @@ int oracle_run(const oracle_params *p, int64_t n, int32_t n_events, const int32_
   int32_t *fcount = NULL, *fpos = NULL, *flocal = NULL, *stack = NULL;
   if (rc == ORACLE_OK) {
     fcount = (int32_t *)calloc((size_t)n + 1, sizeof(int32_t));
-    fpos = (int32_t *)malloc((size_t)n * sizeof(int32_t));
+    /* one more: an event without hits at the end still writes its first start */
+    fpos = (int32_t *)malloc(((size_t)n + 1) * sizeof(int32_t));
     flocal = (int32_t *)malloc((size_t)n * sizeof(int32_t));
     stack = (int32_t *)malloc((size_t)n * sizeof(int32_t));
     if (!fcount || !fpos || !flocal || !stack) rc = ORACLE_ERR_NOMEM;
