@@ -185,6 +185,8 @@ hipError_t launch_pipeline(const Geom& g, const Arena& a, const RunDesc& d, cons
                            hipStream_t s, hipEvent_t* ev);
 hipError_t launch_direct(const Geom& g, const Arena& a, const RunDesc& d, hipStream_t s, hipEvent_t* ev);
 hipError_t launch_set_desc(const RunDesc& d, RunDesc* dd, hipStream_t s);
+// ids[start[e] - start[0] .. start[e + 1] - start[0]) = first + e for e in [0, events).
+hipError_t launch_event_ids(int32_t* ids, const int64_t* start, int32_t first, int32_t events, hipStream_t s);
 hipError_t launch_validate(const Geom& g, const Arena& a, const RunDesc& d, hipStream_t s);
 int occupancy_blocks_per_cu(int which, int lds_bytes);
 int lds_bytes_for(const Geom& g);

@@ -1900,6 +1900,30 @@ __global__ __launch_bounds__(kWG) void k_validate(RunDesc d, int L, uint32_t* er
   if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(err, (uint32_t)E_INPUT);
 }
 
+// Event ids of a chunk of the host-resident form, for up to kIdEvents events a
+// launch, whose first hits travel in the kernel's arguments. Bound by its
+// stores (4 bytes a hit), which overlap the next chunk's copy.
+constexpr int kIdEvents = 128;
+struct EventStarts {
+  int32_t start[kIdEvents + 1];
+};
+__global__ __launch_bounds__(kWG) void k_event_ids(int32_t* ids, EventStarts s, int32_t first, int events) {
+  __shared__ int32_t st[kIdEvents + 1];
+  for (int i = threadIdx.x; i <= events; i += kWG) st[i] = s.start[i];
+  __syncthreads();
+  for (int h = st[0] + blockIdx.x * kWG + threadIdx.x; h < st[events]; h += gridDim.x * kWG) {
+    int lo = 0, hi = events - 1;  // the last event that starts at or before h
+    while (lo < hi) {
+      const int mid = (lo + hi + 1) >> 1;
+      if (st[mid] <= h)
+        lo = mid;
+      else
+        hi = mid - 1;
+    }
+    ids[h] = first + lo;
+  }
+}
+
 __global__ void k_set_desc(RunDesc d, RunDesc* dd) {
   if (threadIdx.x == 0) *dd = d;
 }
@@ -2024,6 +2048,19 @@ hipError_t launch_pipeline(const Geom& g, const Arena& a, const RunDesc& d, cons
 
 hipError_t launch_set_desc(const RunDesc& d, RunDesc* dd, hipStream_t s) {
   k_set_desc<<<1, 64, 0, s>>>(d, dd);
+  return hipGetLastError();
+}
+
+hipError_t launch_event_ids(int32_t* ids, const int64_t* start, int32_t first, int32_t events, hipStream_t s) {
+  for (int32_t e = 0; e < events; e += kIdEvents) {
+    const int ne = std::min(events - e, kIdEvents);
+    EventStarts st;
+    for (int i = 0; i <= ne; ++i) st.start[i] = (int32_t)(start[e + i] - start[0]);
+    const int64_t n = st.start[ne] - st.start[0];
+    if (n == 0) continue;
+    const int grid = (int)std::min<int64_t>(cdiv(n, kWG), 1024);
+    k_event_ids<<<grid, kWG, 0, s>>>(ids, st, first + e, ne);
+  }
   return hipGetLastError();
 }
 
