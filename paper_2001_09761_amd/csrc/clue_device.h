@@ -141,7 +141,7 @@ __device__ __forceinline__ int event_of_slot(const Geom& g, const Arena& a, cons
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ bool unit_space(const Geom& g, const RunDesc& d) {
   const int64_t n = d.n, U = (int64_t)d.n_events * g.L, side = 2 * g.halo + 1;
-  const int64_t spill = n * side * side / g.lds_cap + n * g.tpq / kWG + 1;
+  const int64_t spill = n * side * side / g.lds_cap + n / kWG + 1;
   return spill + 2 * U + g.units + 1 <= n && (int64_t)g.L * kUnitMax <= (int64_t)kPackedEventMax &&
          n <= U * kUnitAvg;
 }
