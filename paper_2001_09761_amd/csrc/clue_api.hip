@@ -76,7 +76,7 @@ static inline bool finite(float v) { return std::isfinite(v); }
 // Geometry: tile size, halo and window bounds.
 // ---------------------------------------------------------------------------
 static int plan_geom(const clue_params& p, float tile, int tpq, int bx, int by, int lds_cap, float r1, int quads,
-                     int expansion, Geom& g, std::string& msg) {
+                     int expansion, Geom& g, std::string& msg, int max_block = 16) {
   if (!finite(p.dc) || !(p.dc > 0.0f) || !finite(p.rho_c) || !finite(p.delta_c) || !finite(p.delta_o) ||
       p.delta_c < 0.0f || p.delta_o < 0.0f) {
     msg = "invalid clustering parameters (need finite dc > 0, rho_c, delta_c >= 0, delta_o >= 0)";
@@ -100,7 +100,7 @@ static int plan_geom(const clue_params& p, float tile, int tpq, int bx, int by, 
     msg = "threads_per_query must be 1, 2, 4 or 8";
     return CLUE_ERR_ARG;
   }
-  if (bx < 1 || by < 1 || bx > 16 || by > 16) {
+  if (bx < 1 || by < 1 || bx > max_block || by > max_block) {
     msg = "tile block must be within 1..16 tiles per side";
     return CLUE_ERR_ARG;
   }
@@ -211,17 +211,28 @@ static int units_grid(const Geom& g, int64_t n, int64_t capacity) {
 // of the paper's workload at its 5 cm bin: density 288 us with 5 cm tiles, 88 us
 // with 6.05 cm ones).
 //
+// Sparse layers: tiles grow by up to a quarter towards 1.8 hits each, because a
+// tile costs its share of the grid and of the quad lists whether or not it holds
+// hits (16 events of 100 layers of 300 hits: 337 us, grown 238; of 1400: 411 and
+// 326; one event of 1000 a layer: 80 and 79). Not further, for a query's lists grow
+// with the tile's area where a layer's hits lie close together (60 % of 1900 hits
+// within 20 cm: 314 us, 253 grown by a quarter, 448 by a half), and only where a
+// layer holds at most twice the cap on average (3000 hits a layer gain nothing).
+//
 // Block: as many tiles a side as make its region (block and halo) hold 620 hits
-// on average, at most 10. At the default cap of 960 hits, that leaves room for
-// the layers' and clusters' fluctuations, for a region over the cap is staged in
-// halves. A run of 1M hits on 100 layers (4 hits per tile) took 189, 172 and
-// 203 us with blocks of 8, 10 and 12, the paper's (8.6 per tile) 263, 284, 294
-// and 306 us with 5, 6, 7 and 8, and 100,000 hits (0.4 per tile) 113, 93 and 93
-// us with 8, 10 and 16. Smaller blocks, down to 8, where there would be less than
-// four items per CU.
+// on average, at most 24 with the halo. At the default cap of 960 hits, that
+// leaves room for the layers' and clusters' fluctuations, for a region over the
+// cap is staged in halves. A run of 1M hits on 100 layers (4 hits per tile) took
+// 189, 172 and 203 us with blocks of 8, 10 and 12, the paper's (8.6 per tile) 263,
+// 284, 294 and 306 us with 5, 6, 7 and 8. A block costs 12 us of a workgroup's time
+// however few hits it holds: 16 events of 100 layers of 3000 hits (1.2 per tile)
+// took 821 us with blocks of 10, 666 with 13 and 570 with 17. The blocks are made
+// equally large (33 tiles a side in three blocks of 11: 91 us, of 16, 16 and 1: 101),
+// and smaller, down to 8, where there would be less than three items per CU (100
+// layers of 1900 hits: 93 us with 900 blocks, 102 with 400).
 static Geom run_geom(const clue_params& p, const Geom& req, int tpq, int lds_cap, float r1, int quads,
                      int expansion, double n, double units) {
-  constexpr double kRegionHits = 620.0;
+  constexpr double kRegionHits = 620.0, kTileHits = 1.8;
   std::string msg;
   float tile = p.tile_size;
   Geom g = req;
@@ -229,12 +240,24 @@ static Geom run_geom(const clue_params& p, const Geom& req, int tpq, int lds_cap
     tile = (float)(2.0 * (double)p.dc * (1.0 + 1.0 / 128.0));
     if (plan_geom(p, tile, tpq, 1, 1, lds_cap, r1, quads, expansion, g, msg) != CLUE_OK) return req;
   }
+  if (n <= units * 2.0 * lds_cap) {
+    const double grow = std::min(1.25, std::sqrt(kTileHits * units * g.tpl / std::max(n, 1.0)));
+    if (grow > 1.0) {
+      tile = (float)(grow / (double)g.inv_t);
+      if (plan_geom(p, tile, tpq, 1, 1, lds_cap, r1, quads, expansion, g, msg) != CLUE_OK) return req;
+    }
+  }
   const double per_tile = n / (units * g.tpl);
-  int b = 10;
-  if (per_tile * (10.0 + 2 * g.halo) * (10.0 + 2 * g.halo) > kRegionHits)
+  const double most = std::max(8, 24 - 2 * g.halo);
+  int b = (int)most;
+  if (per_tile * (most + 2 * g.halo) * (most + 2 * g.halo) > kRegionHits)
     b = std::max(1, (int)std::sqrt(kRegionHits / per_tile) - 2 * g.halo);
-  while (b > 8 && units * ((g.nx + b - 1) / b) * ((g.ny + b - 1) / b) < 1024.0) --b;
-  if (plan_geom(p, tile, tpq, b, b, lds_cap, r1, quads, expansion, g, msg) != CLUE_OK) return req;
+  while (b > 8 && units * ((g.nx + b - 1) / b) * ((g.ny + b - 1) / b) < 800.0) --b;
+  auto even = [b](int tiles) {
+    const int blocks = (tiles + b - 1) / b;
+    return (tiles + blocks - 1) / blocks;
+  };
+  if (plan_geom(p, tile, tpq, even(g.nx), even(g.ny), lds_cap, r1, quads, expansion, g, msg, 24) != CLUE_OK) return req;
   return g;
 }
 

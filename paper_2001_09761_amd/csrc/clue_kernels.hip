@@ -526,16 +526,16 @@ __device__ __forceinline__ int slot_of(const RegionLds& L, int row, int p) { ret
 // stages 2 x 84 tiles instead of 4 x 49 (one event of uneven layers, whose
 // densest overflow a 10 x 10 block: density 67 -> 53 us, nearest-higher 76 ->
 // 57 us; the paper's workload, 1M hits of 3 cm clusters: 828 -> 614 us a run).
-// Rectangles are relative to the block (at most 16 tiles a side), four bits per
-// bound; those still to do wait on an LDS stack (each halving of at most 4 + 4
+// Rectangles are relative to the block (at most 32 tiles a side), eight bits per
+// bound; those still to do wait on an LDS stack (each halving of at most 5 + 5
 // leaves one). Every lane keeps the same state; lane 0 writes the stack, and
 // region_setup's barriers lie between any write and read of one entry.
 struct BlockWalk {
   int x0, y0, x1, y1;  // the current rectangle, inclusive
   int depth;
-  unsigned short* stack;
-  static constexpr int kDepth = 8;
-  __device__ __forceinline__ BlockWalk(unsigned short* s, int w, int h)
+  unsigned* stack;
+  static constexpr int kDepth = 10;
+  __device__ __forceinline__ BlockWalk(unsigned* s, int w, int h)
       : x0(0), y0(0), x1(w - 1), y1(h - 1), depth(0), stack(s) {}
   __device__ __forceinline__ bool single() const { return x0 == x1 && y0 == y1; }
   // Keeps the first half as the current rectangle.
@@ -543,7 +543,7 @@ struct BlockWalk {
     const bool wide = x1 - x0 >= y1 - y0;
     const int mx = (x0 + x1) >> 1, my = (y0 + y1) >> 1;
     if (threadIdx.x == 0)
-      stack[depth] = (unsigned short)((wide ? mx + 1 : x0) | (wide ? y0 : my + 1) << 4 | x1 << 8 | y1 << 12);
+      stack[depth] = (unsigned)((wide ? mx + 1 : x0) | (wide ? y0 : my + 1) << 8 | x1 << 16 | y1 << 24);
     ++depth;
     x1 = wide ? mx : x1;
     y1 = wide ? y1 : my;
@@ -552,10 +552,10 @@ struct BlockWalk {
   __device__ __forceinline__ bool next() {
     if (depth == 0) return false;
     const unsigned v = stack[--depth];
-    x0 = v & 15;
-    y0 = (v >> 4) & 15;
-    x1 = (v >> 8) & 15;
-    y1 = v >> 12;
+    x0 = v & 255;
+    y0 = (v >> 8) & 255;
+    x1 = (v >> 16) & 255;
+    y1 = v >> 24;
     return true;
   }
 };
@@ -903,12 +903,15 @@ static_assert(kMaxRegionRows <= 64 && kMaxRegionTiles <= 1024, "a staged tile id
 // 2x2 tile quad anchored at its lower-left window tile; the quads a core
 // query can use are merged once per region into index-ordered lists (byte
 // offsets of the records), so each query is one linear scan in ascending
-// hit index. Otherwise (or if the quads do not fit) a query merges its
-// window's tile lists itself.
+// hit index. Where the quads do not fit, false is returned with nothing done and
+// the caller halves the block (the merges below cost more than the second
+// staging: 100 layers with 900 of 1000 hits in 10 cm, 620 -> 165 us); a `single`
+// tile, or a window of three tiles, takes those: a query merges its window's
+// tile lists itself.
 template <int MAXL, int K>
-__device__ __forceinline__ void density_staged(const Geom& g, const Arena& a, const Region& R, RegionLds& L,
+__device__ __forceinline__ bool density_staged(const Geom& g, const Arena& a, const Region& R, RegionLds& L,
                                                const Staged<MAXL>& S, unsigned short* stile, unsigned short* qidx,
-                                               unsigned short sent, bool keep) {
+                                               unsigned short sent, bool keep, bool single) {
   const int per_row = R.rw + 1;
   const int64_t ubase = (int64_t)R.unit * g.tpl;
   const int ntl = R.rh * per_row;
@@ -980,6 +983,7 @@ __device__ __forceinline__ void density_staged(const Geom& g, const Arena& a, co
     }
   }
   __syncthreads();
+  if (use_quads && *L.qtotal > 4 * g.lds_cap && !single) return false;
   if (use_quads && *L.qtotal <= 4 * g.lds_cap && g.density_quads == 2) {
     // one lane per quad: a sequential merge of its (up to four) index-sorted
     // tile lists
@@ -1190,6 +1194,7 @@ __device__ __forceinline__ void density_staged(const Geom& g, const Arena& a, co
     a.rho[slot] = rho;
     if (keep) a.rho_out[S.key(p)] = rho;
   }
+  return true;
 }
 
 // Regions whose tiles are too dense for LDS are not searched by the workgroup
@@ -1371,7 +1376,7 @@ __global__ __launch_bounds__(kWG, density_min_waves(MAXL, K)) void k_density(Des
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ int s_rows[kRowMetaInts];
   __shared__ int s_item;
-  __shared__ unsigned short s_stack[BlockWalk::kDepth];
+  __shared__ unsigned s_stack[BlockWalk::kDepth];
   const Staged<MAXL> S{smem, g.lds_cap};
   unsigned short* stile = reinterpret_cast<unsigned short*>(smem + 16 * g.lds_cap);  // both layouts: 16 B per hit
   unsigned short* qidx = reinterpret_cast<unsigned short*>(smem + density_qidx_offset(g.lds_cap));
@@ -1395,7 +1400,10 @@ __global__ __launch_bounds__(kWG, density_min_waves(MAXL, K)) void k_density(Des
       region_setup(g, a, R, L);
       if (L.core_lo[R.ch] > 0) {
         if (R.total <= g.lds_cap) {
-          density_staged<MAXL, K>(g, a, R, L, S, stile, qidx, sent, keep);
+          if (!density_staged<MAXL, K>(g, a, R, L, S, stile, qidx, sent, keep, B.single())) {
+            B.split();
+            continue;
+          }
         } else if (B.single()) {
           spill_region(g, a, R, C_SPILL_RHO, kWG);
         } else {
@@ -1713,7 +1721,7 @@ __device__ __forceinline__ void nh_global_region(const Geom& g, const Arena& a, 
 template <bool STRICT>
 __device__ __forceinline__ void nh_item(const Geom& g, const Arena& a, const RunDesc& d, int item, RegionLds& L,
                                         float4* rec, unsigned short* queue, unsigned char* prow, unsigned short* coreq,
-                                        int* s_qn, int* s_counts, unsigned short* s_stack, int& unit) {
+                                        int* s_qn, int* s_counts, unsigned* s_stack, int& unit) {
   int tx0, ty0, tx1, ty1;
   item_block(g, item, unit, tx0, ty0, tx1, ty1);
   const int e = unit / g.L;
@@ -1823,7 +1831,7 @@ __global__ __launch_bounds__(kWG, 8) void k_nearest_higher(DescArg<G> dg, Geom g
   __shared__ int s_rows[kRowMetaInts];
   __shared__ int s_qn;
   __shared__ int s_item;
-  __shared__ unsigned short s_stack[BlockWalk::kDepth];
+  __shared__ unsigned s_stack[BlockWalk::kDepth];
   float4* rec = reinterpret_cast<float4*>(smem);
   unsigned short* queue = reinterpret_cast<unsigned short*>(rec + g.lds_cap);
   unsigned short* coreq = queue + g.lds_cap;

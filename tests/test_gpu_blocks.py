@@ -30,3 +30,25 @@ def test_block_shapes_over_the_cap(event, block, cap, batched):
     ev, ref = event
     tuning = dict(block_x=block[0], block_y=block[1], lds_cap=cap, plain_lds_cap=cap)
     assert_parity(gpu_run(ev, P, batched=batched, tuning=tuning), ref, where=f"{block} cap {cap}")
+
+
+@pytest.mark.parametrize("bounds", [(0, 0, 200, 200), (-30, 10, 170, 60), (0, 0, 9, 400)], ids=str)
+@pytest.mark.parametrize("per_layer", [60, 700, 2500])
+@pytest.mark.parametrize("spot", [0.0, 0.9])
+def test_sparse_layers_take_large_blocks(bounds, per_layer, spot):
+    """Untuned runs of sparse layers take blocks of up to 22 tiles a side and grown tiles; with most
+    hits of a layer in one spot, the blocks are halved from there down to single tiles."""
+    rng = np.random.default_rng(per_layer)
+    n_layers = 9000 // per_layer + 2
+    n = n_layers * per_layer
+    x0, y0, x1, y1 = bounds
+    x, y = rng.uniform(x0, x1, n), rng.uniform(y0, y1, n)
+    s = rng.random(n) < spot
+    x[s], y[s] = rng.normal(x0 + 6, 2.0, s.sum()), rng.normal(y1 - 20, 2.0, s.sum())
+    ev = dict(x=x.astype(np.float32), y=y.astype(np.float32), layer=np.repeat(np.arange(n_layers, dtype=np.int32), per_layer),
+              energy=rng.uniform(0.1, 2.0, n).astype(np.float32))
+    p = dict(P, bounds=bounds, n_layers=n_layers)
+    ref = oracle.run(ev["x"], ev["y"], ev["layer"], ev["energy"], dc=2.0, rho_c=5.0, delta_c=2.0, delta_o=4.0,
+                     bounds=bounds, n_layers=n_layers, n_threads=min(16, os.cpu_count() or 1))
+    for batched in (False, True):
+        assert_parity(gpu_run(ev, p, batched=batched), ref, where=f"{bounds} {per_layer} {spot} {batched}")
