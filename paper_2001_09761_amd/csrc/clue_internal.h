@@ -185,6 +185,16 @@ hipError_t launch_pipeline(const Geom& g, const Arena& a, const RunDesc& d, cons
                            hipStream_t s, hipEvent_t* ev);
 hipError_t launch_direct(const Geom& g, const Arena& a, const RunDesc& d, hipStream_t s, hipEvent_t* ev);
 hipError_t launch_set_desc(const RunDesc& d, RunDesc* dd, hipStream_t s);
+// Up to three arrays of n 4-byte words copied src -> dst (null: not copied), and one
+// word on its own (null: none).
+struct ReadOut {
+  const void* src[3];
+  void* dst[3];
+  int64_t n[3];
+  const int32_t* word;
+  int32_t* word_out;
+};
+hipError_t launch_read_out(const ReadOut& r, hipStream_t s);
 // ids[start[e] - start[0] .. start[e + 1] - start[0]) = first + e for e in [0, events).
 hipError_t launch_event_ids(int32_t* ids, const int64_t* start, int32_t first, int32_t events, hipStream_t s);
 hipError_t launch_validate(const Geom& g, const Arena& a, const RunDesc& d, hipStream_t s);

@@ -2070,6 +2070,24 @@ __global__ __launch_bounds__(kWG) void k_validate(RunDesc d, int L, uint32_t* er
   if (__any(bad) && (threadIdx.x & 63) == 0) atomicOr(err, (uint32_t)E_INPUT);
 }
 
+// Copies a run's arrays out, one row of workgroups each. Sixteen bytes a lane
+// where the destination is aligned for it, as the sources are; bound by the
+// launch below about a million hits, by memory above.
+__global__ __launch_bounds__(kWG) void k_read_out(ReadOut r) {
+  const int k = blockIdx.y;
+  const int64_t first = (int64_t)blockIdx.x * kWG + threadIdx.x, step = (int64_t)gridDim.x * kWG, n = r.n[k];
+  if (k == 0 && first == 0 && r.word_out) *r.word_out = *r.word;
+  const uint32_t* const src = (const uint32_t*)r.src[k];
+  uint32_t* const dst = (uint32_t*)r.dst[k];
+  if (!dst) return;
+  int64_t done = 0;
+  if (((uintptr_t)src | (uintptr_t)dst) % 16 == 0) {
+    done = n & ~(int64_t)3;
+    for (int64_t i = first; i < n / 4; i += step) ((uint4*)dst)[i] = ((const uint4*)src)[i];
+  }
+  for (int64_t i = done + first; i < n; i += step) dst[i] = src[i];
+}
+
 // Event ids of a chunk of the host-resident form, for up to kIdEvents events a
 // launch, whose first hits travel in the kernel's arguments. Bound by its
 // stores (4 bytes a hit), which overlap the next chunk's copy.
@@ -2218,6 +2236,15 @@ hipError_t launch_pipeline(const Geom& g, const Arena& a, const RunDesc& d, cons
 
 hipError_t launch_set_desc(const RunDesc& d, RunDesc* dd, hipStream_t s) {
   k_set_desc<<<1, 64, 0, s>>>(d, dd);
+  return hipGetLastError();
+}
+
+hipError_t launch_read_out(const ReadOut& r, hipStream_t s) {
+  int64_t most = 1;
+  for (int k = 0; k < 3; ++k)
+    if (r.dst[k]) most = std::max(most, r.n[k]);
+  const dim3 grid((unsigned)std::min<int64_t>(cdiv(cdiv(most, 4), kWG), 2048), r.src[2] ? 3 : 2);
+  k_read_out<<<grid, kWG, 0, s>>>(r);
   return hipGetLastError();
 }
 
