@@ -68,10 +68,11 @@ def code_sha(sources) -> str:
 
 
 def kernel_source_sha() -> str:
-    """Code hash of the kernel source and the internal header it includes:
+    """Code hash of the kernel sources and the internal headers they include:
     profiles stay valid across edits that change no code."""
     return code_sha(open(os.path.join(ROOT, "paper_2001_09761_amd", "csrc", f)).read()
-                    for f in ("clue_kernels.hip", "clue_internal.h"))
+                    for f in ("clue_kernels.hip", "clue_units.hip", "clue_direct.hip", "clue_device.h",
+                              "clue_internal.h"))
 
 
 def percentile(v, q):
@@ -539,10 +540,21 @@ def main():
     print(json.dumps(out), flush=True)
 
 
-STAGE_KERNEL = {"clear": "k_clear<true", "grid_hist": "k_hist<true", "grid_scan": "k_scan<true, 0>",
-                "grid_scatter": "k_scatter<true", "grid_place": "k_place<true", "density": "k_density<true",
-                "nearest_higher": "k_nearest_higher<true", "seed_scan": "k_scan<true, 2>", "labels": "k_label<true",
-                "follower_lists": "k_follow_sort<true"}
+# The batched kernel of every stage; where hits that come grouped by layer take a
+# kernel of their own, that one first.
+STAGE_KERNEL = {"clear": ("k_units<true", "k_clear<true"), "grid_hist": ("k_unit_sort<true", "k_hist<true"),
+                "grid_scan": ("k_scan<true, 0>",), "grid_scatter": ("k_scatter<true",),
+                "grid_place": ("k_place<true",), "density": ("k_density<true",),
+                "nearest_higher": ("k_nearest_higher<true",), "seed_scan": ("k_scan<true, 2>",),
+                "labels": ("k_unit_finish<true", "k_label<true"), "follower_lists": ("k_follow_sort<true",)}
+
+
+def stage_kernel(stage, names):
+    """The kernel match of a stage among the profiled kernel names."""
+    for m in STAGE_KERNEL[stage]:
+        if any(m in n for n in names):
+            return m
+    return STAGE_KERNEL[stage][-1]
 
 
 def _pmc_rows(d):
@@ -572,9 +584,11 @@ def traffic_summary(d, stage, n_events, out_path=None):
     WRITE_SIZE (KiB per dispatch) averaged over its dispatches, each scaled by
     the ratio of known bytes to what the same counter reads for the 1 GiB
     elementwise copy (torch.neg)."""
-    kname = STAGE_KERNEL[stage]
-    f_k, nf = _mean_counter(_pmc_rows(os.path.join(d, "fetch")), "FETCH_SIZE", kname)
-    w_k, nw = _mean_counter(_pmc_rows(os.path.join(d, "write")), "WRITE_SIZE", kname)
+    fetch_rows, write_rows = _pmc_rows(os.path.join(d, "fetch")), _pmc_rows(os.path.join(d, "write"))
+    names = {r[0] for r in fetch_rows}
+    kname = stage_kernel(stage, names)
+    f_k, nf = _mean_counter(fetch_rows, "FETCH_SIZE", kname)
+    w_k, nw = _mean_counter(write_rows, "WRITE_SIZE", kname)
     f_c, _ = _mean_counter(_pmc_rows(os.path.join(d, "copy_fetch")), "FETCH_SIZE", "neg")
     w_c, _ = _mean_counter(_pmc_rows(os.path.join(d, "copy_write")), "WRITE_SIZE", "neg")
     gib = float(1 << 30)
@@ -582,9 +596,9 @@ def traffic_summary(d, stage, n_events, out_path=None):
     hbm = f_k * 1024.0 * sf + w_k * 1024.0 * sw
     hits = 10000 * 100 * n_events
     # every stage's batched kernel, for the whole-pipeline measured traffic
-    fetch_rows, write_rows = _pmc_rows(os.path.join(d, "fetch")), _pmc_rows(os.path.join(d, "write"))
     per_stage = {}
-    for st, km in STAGE_KERNEL.items():
+    for st in STAGE_KERNEL:
+        km = stage_kernel(st, names)
         try:
             fs_k, _ = _mean_counter(fetch_rows, "FETCH_SIZE", km)
             ws_k, _ = _mean_counter(write_rows, "WRITE_SIZE", km)
@@ -609,8 +623,9 @@ def issue_summary(d, stage, n_events, out_path=None):
     wave64 instruction per CU-cycle."""
     import csv
     import glob
-    kname = STAGE_KERNEL[stage]
-    valu, nv = _mean_counter(_pmc_rows(os.path.join(d, "sq")), "SQ_INSTS_VALU", kname)
+    rows = _pmc_rows(os.path.join(d, "sq"))
+    kname = stage_kernel(stage, {r[0] for r in rows})
+    valu, nv = _mean_counter(rows, "SQ_INSTS_VALU", kname)
     durs = []
     for f in glob.glob(os.path.join(d, "ktrace", "**", "*kernel_stats.csv"), recursive=True):
         with open(f) as fh:

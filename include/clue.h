@@ -127,7 +127,8 @@ int clue_footprint_bytes(const clue_params *p, int64_t max_hits, int32_t max_eve
  * x, y, energy float32[n]; layer int32[n]; outputs cluster_id int32[n] and
  * is_seed uint8[n]. All are DEVICE pointers owned by the caller. `stream` is a
  * hipStream_t (NULL: the default stream). n == 0 is a no-op. Launches one
- * kernel per stage sized to the event ("plain" form).
+ * kernel per stage sized to the event ("plain" form); up to 8192 hits take
+ * three kernels that compare all pairs, unless a tuning has been set.
  */
 int clue_run(clue_ctx *c, int64_t n, const float *x, const float *y, const int32_t *layer,
              const float *energy, int32_t *cluster_id, uint8_t *is_seed, void *stream);
@@ -139,7 +140,8 @@ int clue_run(clue_ctx *c, int64_t n, const float *x, const float *y, const int32
  * are event-local, identical to running each event alone. Sec. 3 processes
  * all layers of one event in each kernel launch; this extends that to many
  * events: one persistent kernel per stage over a device work queue of
- * (event, layer, tile block) items, replayed from a captured HIP graph.
+ * (event, layer, tile block) items, replayed from a captured HIP graph. Small
+ * batches (up to 4M hits) are launched as clue_run is, sized to the batch.
  * Errors as clue_run, plus CLUE_ERR_ARG for a null `event` with n_events > 1;
  * ids out of range or decreasing are caught only with CLUE_VALIDATE (without
  * it the run stays within its buffers, with unspecified results).

@@ -3,7 +3,8 @@
 // Stage map (arXiv:2001.09761):
 //   k_clear            clears counters, tile counts and scan status
 //   (k_units, k_unit_sort and k_unit_finish, in clue_units.hip, take the place of
-//   the other grid-build and label kernels when the hits come grouped by layer)
+//   the other grid-build and label kernels when the hits come grouped by layer;
+//   runs of few hits take the kernels of clue_direct.hip instead of all of these)
 //   k_hist             fixed grid, part 1: atomic per-tile histogram (Sec. 2.1)
 //   k_scan<TILES>      exclusive prefix scan of the tile counts (decoupled look-back)
 //   k_scatter          fixed grid, part 2: hit ids into the tile CSR (arrival order)
@@ -24,6 +25,8 @@
 //   k_expand_init      the k-way alternative to k_label (Algorithm 3): follower
 //   k_expand_dfs       lists, seed list, then one depth-first walk per seed
 //   k_follow_sort      sorts each follower list by hit index, event-local ids
+//   k_event_ids        a host-resident chunk's event ids from its events' first hits
+//   k_read_out         copies intermediates or follower lists to the caller
 //
 // Every float operation that decides a result is an explicit round-to-nearest
 // intrinsic (no contraction), so results match a plain IEEE binary32
