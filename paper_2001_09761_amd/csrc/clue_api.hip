@@ -745,14 +745,17 @@ int clue_run_batch_host(clue_ctx* c, int64_t n, int32_t n_events, const int32_t*
   if (rc != CLUE_OK) return rc;
   // The device writes the event ids from the events' first hits: the copies in,
   // which the form is bound by, are 16 bytes a hit instead of 20: 3.81 ms before,
-  // 3.05 ms now for 16 events of 500,000 hits. Ids that are to be checked are
-  // copied. (Chunks of 1M hits instead of the whole capacity: 3.21 ms.)
-  const bool copy_ids = event && (c->params.flags & CLUE_VALIDATE);
+  // 3.05 ms now for 16 events of 500,000 hits. (Chunks of 1M hits instead of the
+  // whole capacity: 3.21 ms.) Ids are copied where they are to be checked, and for
+  // events of less than 512 hits on average: a launch writes 128 events' ids and
+  // costs about 4 us, in which 57,000 ids are copied.
+  const bool check_ids = c->params.flags & CLUE_VALIDATE;
   for (size_t k = 0; k < chunks.size(); ++k) {
     const int slot = (int)(k & 1);
     const StageChunk sc = stage_chunk(c, slot);
     const int32_t e0 = chunks[k].first, ne = chunks[k].second;
     const int64_t h0 = start[e0], nh = start[e0 + ne] - h0;
+    const bool copy_ids = event && (check_ids || nh < (int64_t)512 * ne);
     if (k >= 2) HIP_TRY(c, hipStreamWaitEvent(c->h2d, c->done[slot], 0));  // inputs of chunk k - 2 consumed
     HIP_TRY(c, hipMemcpyAsync(sc.x, x + h0, nh * 4, hipMemcpyHostToDevice, c->h2d));
     HIP_TRY(c, hipMemcpyAsync(sc.y, y + h0, nh * 4, hipMemcpyHostToDevice, c->h2d));

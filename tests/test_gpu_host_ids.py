@@ -1,5 +1,6 @@
 """The host-resident form's event ids, which the device writes from the events'
-first hits: more events than one launch of that kernel takes, empty events at
+first hits where events hold 512 hits or more on average, and which are copied
+otherwise: more events than one launch of that kernel takes, empty events at
 both ends and in runs, chunks of one event and of many, against the oracle; and
 CLUE_VALIDATE, which checks the caller's own ids."""
 import os
@@ -14,12 +15,12 @@ pytestmark = pytest.mark.gpu
 P = dict(dc=2.0, rho_c=5.0, delta_c=2.0, delta_o=4.0, bounds=(0, 0, 20, 20), n_layers=2)
 
 
-def _batch(n_events):
+def _batch(n_events, most=60):
     rng = np.random.default_rng(n_events)
-    sizes = rng.integers(0, 60, n_events)
+    sizes = rng.integers(0, most, n_events)
     sizes[rng.random(n_events) < 0.4] = 0
     sizes[[0, -1]] = 0
-    sizes[n_events // 2] = 500
+    sizes[n_events // 2] = max(500, 2 * most)
     evs = [{k: v[:s] for k, v in adversarial_event(i, n=max(int(s), 20), n_layers=2).items()}
            for i, s in enumerate(sizes)]
     b = {k: np.concatenate([e[k] for e in evs]) for k in ("x", "y", "layer", "energy")}
@@ -29,9 +30,10 @@ def _batch(n_events):
 
 @pytest.mark.parametrize("n_events", [3, 127, 128, 129, 300])
 @pytest.mark.parametrize("cap_events", [1, 7, 1000])
-def test_ids_written_on_the_device(n_events, cap_events):
+@pytest.mark.parametrize("most", [60, 3000])
+def test_ids_of_chunks(n_events, cap_events, most):
     import paper_2001_09761_amd as clue
-    b, sizes = _batch(n_events)
+    b, sizes = _batch(n_events, most)
     ref = oracle.run(b["x"], b["y"], b["layer"], b["energy"], dc=2.0, rho_c=5.0, delta_c=2.0, delta_o=4.0,
                      bounds=P["bounds"], n_layers=2, event=b["event"], n_events=n_events,
                      n_threads=min(16, os.cpu_count() or 1))
