@@ -604,10 +604,18 @@ static int run_common(clue_ctx* c, int64_t n, int32_t n_events, int32_t event_ba
   // A batched run of a context with room for larger ones captures the graph even
   // where it does not replay it, so that one run warms a context up: a served
   // stream whose first large batch captured it had a p99 of 5.1 ms, 1.3 ms now.
-  if (batched && !ev && (c->a.cap_hits > kSizedMaxHits ||
-                         (int64_t)c->a.cap_events * c->g_batch.L * c->g_batch.bpu > kSizedMaxItems)) {
-    rc = ensure_graph(c);
-    if (rc != CLUE_OK) return rc;
+  // (Not within the caller's own capture, which records plain launches.)
+  if (batched && !ev && !c->exec &&
+      (c->a.cap_hits > kSizedMaxHits || (int64_t)c->a.cap_events * c->g_batch.L * c->g_batch.bpu > kSizedMaxItems)) {
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(s, &st) != hipSuccess) {
+      (void)hipGetLastError();
+      st = hipStreamCaptureStatusActive;
+    }
+    if (st == hipStreamCaptureStatusNone) {
+      rc = ensure_graph(c);
+      if (rc != CLUE_OK) return rc;
+    }
   }
   if (!c->tuned && n <= kDirectMax) {
     HIP_TRY(c, launch_direct(c->g, c->a, d, s, ev));

@@ -160,3 +160,51 @@ def test_small_runs_of_many_items_by_the_graph(tuning, order):
     p = dict(P, n_layers=3)
     t = dict(dict(block_x=1, block_y=1, tile_size=4.03125), **tuning)
     assert_parity(gpu_run(b, p, batched=True, n_events=160, tuning=t), _ref(b, p), where=f"{tuning} {order}")
+
+
+@pytest.mark.parametrize("n_per_layer", [700, 3000], ids=["all pairs", "tiles"])
+@pytest.mark.parametrize("warm", [False, True])
+def test_small_batch_under_capture(n_per_layer, warm):
+    """A small batch captured by the caller, as a context's first run and after one, in a context with room
+    for batches that replay the context's own graph. Replayed over grouped and shuffled hits in turn, with
+    eager runs between, every replay equals the oracle."""
+    import torch
+    import paper_2001_09761_amd as clue
+    dev = torch.device("cuda", 0)
+    p = dict(P, n_layers=3)
+
+    def draw(seed, shuffled):
+        ev = _layers([n_per_layer] * 3, seed)
+        if shuffled:
+            q = np.random.default_rng(seed).permutation(ev["x"].size)
+            ev = {k: v[q] for k, v in ev.items()}
+        return ev
+
+    first = draw(50, False)
+    n = first["x"].size
+    t = {k: torch.from_numpy(v).to(dev) for k, v in first.items()}
+    ids = torch.zeros(n, dtype=torch.int32, device=dev)
+    cid = torch.empty(n, dtype=torch.int32, device=dev)
+    seed_out = torch.empty(n, dtype=torch.uint8, device=dev)
+    with clue.Context(2.0, 5.0, 2.0, 4.0, max_hits=6_000_000, max_events=2, bounds=p["bounds"], n_layers=3) as ctx:
+        args = (ids, 1, t["x"], t["y"], t["layer"], t["energy"], cid, seed_out)
+        if warm:
+            ctx.run_batch(*args)
+            torch.cuda.synchronize()
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph):
+            ctx.run_batch(*args)
+        for i in range(4):
+            ev = draw(60 + i, i % 2 == 1)
+            for k in t:
+                t[k].copy_(torch.from_numpy(ev[k]))
+            graph.replay()
+            torch.cuda.synchronize()
+            ref = _ref(ev, p)
+            for when in ("replay", "eager"):
+                assert np.array_equal(cid.cpu().numpy(), ref["cluster_id"]), (i, when)
+                assert np.array_equal(seed_out.cpu().numpy(), ref["is_seed"].astype(np.uint8)), (i, when)
+                cid.fill_(-9)
+                if when == "replay":
+                    ctx.run_batch(*args)
+                    torch.cuda.synchronize()
