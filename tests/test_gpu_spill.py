@@ -65,3 +65,24 @@ def test_spilled_tiles_strict():
                      n_threads=min(16, os.cpu_count() or 1), **KW)
     assert_parity(gpu_run(ev, KW, flags=clue.KEEP_INTERMEDIATES | clue.TIE_PAPER_STRICT, tuning=dict(lds_cap=256,
                   plain_lds_cap=256)), ref, where="strict")
+
+
+@pytest.mark.parametrize("order", ["layers", "one layer at both ends", "shuffled"])
+@pytest.mark.parametrize("batched", [False, True])
+def test_events_beyond_the_packed_index(order, batched):
+    """An event of more than 2**21 hits: regions whose hits span less than that are staged, counted from their
+    first hit, and the others are searched by the spill kernel."""
+    from paper_2001_09761_amd import gen
+    ev, p = gen.config2(seed=31, event_index=3, n_layers=110, hits_per_layer=20000)
+    n = ev["x"].size
+    assert n > 2 ** 21
+    q = np.arange(n)
+    if order == "one layer at both ends":
+        q = np.concatenate([q[10000:], q[:10000]])  # half of the first layer's hits come last
+    elif order == "shuffled":
+        q = np.random.default_rng(1).permutation(n)
+    ev = {k: np.ascontiguousarray(ev[k][q]) for k in ("x", "y", "layer", "energy")}
+    ref = oracle.run(ev["x"], ev["y"], ev["layer"], ev["energy"], dc=p["dc"], rho_c=p["rho_c"], delta_c=p["delta_c"],
+                     delta_o=p["delta_o"], extent=p["extent"], n_layers=p["n_layers"],
+                     n_threads=min(16, os.cpu_count() or 1))
+    assert_parity(gpu_run(ev, p, batched=batched), ref, where=f"{order} batched {batched}")
