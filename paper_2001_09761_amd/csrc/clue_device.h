@@ -129,31 +129,35 @@ __device__ __forceinline__ int event_of_slot(const Geom& g, const Arena& a, cons
 }
 
 // ---------------------------------------------------------------------------
-// The unit path's arrays. They lie at the ends of the key and rank buffers,
-// which the path leaves free but for the spill queues at their beginnings, so
-// they take no memory of their own; unit_space says whether a run has the room.
-//   key   [n - U - 1, n)           first hit of each of the U units, and n
-//   rank  [n - 2 U, n)             seeds and followers of each unit
-//         [n - 2 U - units, n - 2 U)  each k_units workgroup's verdict
-// A spilled tile's own region (at most 2 halo + 1 tiles a side) holds more than
-// lds_cap hits and a hit lies in at most as many regions, which bounds the tiles;
-// each has one chunk more than its hits fill.
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ bool unit_space(const Geom& g, const RunDesc& d) {
+// The unit path's arrays. They lie in buffers that the path leaves free while it
+// needs them, so they take no memory of their own; unit_space says whether a run
+// has the room.
+//   key   [n - U - 1, n)  first hit of each of the U units, and n
+//   rank  [n - 2 U, n)    seeds and followers of each unit
+//   rho   [0, units)      each k_units workgroup's verdict
+// The key and rank buffers hold the spill queues at their beginnings. A spilled
+// tile's own region (at most 2 halo + 1 tiles a side) holds more than lds_cap hits
+// and a hit lies in at most as many regions, which bounds the tiles; each has one
+// chunk more than its hits fill.
+// Every workgroup of k_unit_sort reads the verdict for itself, the last perhaps
+// after the first have finished, so it must lie where that launch writes nothing:
+// the unit path writes tile_start and the slots' x, y, energy and hit, the general
+// path key, rank, tile_start, event starts and what clear_lists clears. (The unit
+// starts are read by the unit path alone, which does not write key.) The rho buffer
+// is free until the launches after it: k_scatter's pairs, the density.
+__host__ __device__ __forceinline__ bool unit_space(const Geom& g, const RunDesc& d) {
   const int64_t n = d.n, U = (int64_t)d.n_events * g.L, side = 2 * g.halo + 1;
   const int64_t spill = n * side * side / g.lds_cap + n / kWG + 1;
-  return spill + 2 * U + g.units + 1 <= n && (int64_t)g.L * kUnitMax <= (int64_t)kPackedEventMax &&
+  return spill + 2 * U + 1 <= n && g.units <= n && (int64_t)g.L * kUnitMax <= (int64_t)kPackedEventMax &&
          n <= U * kUnitAvg;
 }
-__device__ __forceinline__ int32_t* unit_starts(const Arena& a, const RunDesc& d, const Geom& g) {
+__host__ __device__ __forceinline__ int32_t* unit_starts(const Arena& a, const RunDesc& d, const Geom& g) {
   return a.key + ((int64_t)d.n - (int64_t)d.n_events * g.L - 1);
 }
-__device__ __forceinline__ int32_t* unit_counts(const Arena& a, const RunDesc& d, const Geom& g) {
+__host__ __device__ __forceinline__ int32_t* unit_counts(const Arena& a, const RunDesc& d, const Geom& g) {
   return a.rank + ((int64_t)d.n - 2 * (int64_t)d.n_events * g.L);
 }
-__device__ __forceinline__ int32_t* unit_flags(const Arena& a, const RunDesc& d, const Geom& g) {
-  return unit_counts(a, d, g) - g.units;
-}
+__host__ __device__ __forceinline__ int32_t* unit_flags(const Arena& a) { return reinterpret_cast<int32_t*>(a.rho); }
 // This run takes the unit path (uniform; valid after k_unit_sort).
 __device__ __forceinline__ bool by_units(const Geom& g, const Arena& a) { return g.units && a.counters[C_UNITS]; }
 

@@ -127,7 +127,8 @@ struct Arena {
                          //       of each query chunk)
                          //       (the depth-first expansion reuses both for each
                          //       follower's owner and its position in the owner's list)
-                         //       (the unit path keeps its arrays at their ends)
+                         //       (the unit path keeps its units' first hits and counts
+                         //       at their ends)
                          //       (the grid build keeps (hit id, tile) pairs in arrival
                          //       order in the adjoining rho and parent buffers until
                          //       each tile is ordered by hit index)
@@ -139,6 +140,7 @@ struct Arena {
   float* es;
   int32_t* hs;           // [N]   slot -> caller (batch-global) hit index
   float* rho;            // [N]   slot order; its buffer and the parents' adjoin
+                         //       (the unit path's verdict, until the grid is built)
   int32_t* parent;       // [N]   slot order: nearest-higher slot of a follower, else itself
   uint8_t* flags;        // [N]   slot order: F_SEED | F_OUTLIER | F_FOLLOWER
   uint32_t* seedbits;    // [N/32+2] caller order: one bit per hit, set for seeds

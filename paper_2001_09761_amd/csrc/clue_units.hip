@@ -147,7 +147,7 @@ __global__ __launch_bounds__(kWG) void k_units(DescArg<G> dg, Geom g, Arena a) {
     }
   }
   bad = __syncthreads_or(bad);
-  if (threadIdx.x == 0) unit_flags(a, d, g)[blockIdx.x] = bad;
+  if (threadIdx.x == 0) unit_flags(a)[blockIdx.x] = bad;
 }
 
 // ---------------------------------------------------------------------------
@@ -181,7 +181,7 @@ __global__ __launch_bounds__(kUWG, 8) void k_unit_sort(DescArg<G> dg, Geom g, Ar
   const int lane = tid & 63, wave = tid >> 6;
   bool bad = !unit_space(g, d);
   if (!bad)
-    for (int i = tid; i < g.units; i += kUWG) bad |= unit_flags(a, d, g)[i] != 0;
+    for (int i = tid; i < g.units; i += kUWG) bad |= unit_flags(a)[i] != 0;
   bad = __syncthreads_or(bad);
   if (blockIdx.x == 0 && tid == 0) a.counters[C_UNITS] = !bad;
   if (bad) {
