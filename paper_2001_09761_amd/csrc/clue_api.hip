@@ -210,7 +210,9 @@ static int units_grid(const Geom& g, int64_t n, int64_t capacity) {
 // Tile: where a density window could span three tiles, the next larger tile
 // whose windows span two, because only those take the merged quad lists (1M hits
 // of the paper's workload at its 5 cm bin: density 288 us with 5 cm tiles, 88 us
-// with 6.05 cm ones).
+// with 6.05 cm ones). A requested tile that is no smaller than that stays (far from
+// the origin the coordinates' rounding widens the windows too): the arena is sized
+// for the requested grid, which no run's may exceed.
 //
 // Sparse layers: tiles grow by up to a quarter towards 1.8 hits each, because a
 // tile costs its share of the grid and of the quad lists whether or not it holds
@@ -237,8 +239,9 @@ static Geom run_geom(const clue_params& p, const Geom& req, int tpq, int lds_cap
   std::string msg;
   float tile = p.tile_size;
   Geom g = req;
-  if (req.maxl > 2) {
-    tile = (float)(2.0 * (double)p.dc * (1.0 + 1.0 / 128.0));
+  const float two = (float)(2.0 * (double)p.dc * (1.0 + 1.0 / 128.0));
+  if (req.maxl > 2 && (float)(1.0 / (double)two) < req.inv_t) {
+    tile = two;
     if (plan_geom(p, tile, tpq, 1, 1, lds_cap, r1, quads, expansion, g, msg) != CLUE_OK) return req;
   }
   if (n <= units * 2.0 * lds_cap) {

@@ -1,0 +1,24 @@
+"""The geometry of untuned runs (tile and block from the run's occupancy) fits the
+arena, which is sized for the requested one: checked on the CPU over 200,000 drawn
+extents, distances, tiles and origins."""
+import os
+import subprocess
+import sys
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+sys.path.insert(0, os.path.join(ROOT, "paper_2001_09761_amd"))
+
+
+@pytest.mark.skipif(not os.path.exists("/opt/rocm/bin/hipcc"), reason="hipcc not installed")
+def test_untuned_geometry_fits_the_requested_one(tmp_path):
+    import build as B
+    flags = [f for f in B.FLAGS if f not in ("-shared", "-fPIC", "-O3")]
+    exe = str(tmp_path / "run_geom")
+    cmd = [B.HIPCC, *flags, "-O1", "-I", os.path.join(ROOT, "include"), "-I", B.CSRC,
+           os.path.join(ROOT, "tests", "host_checks", "run_geom.hip"), "-o", exe]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, r.stderr[-2000:]
+    r = subprocess.run([exe], capture_output=True, text=True, timeout=120)
+    assert r.returncode == 0, r.stdout
