@@ -193,15 +193,14 @@ static int plan_geom(const clue_params& p, float tile, int tpq, int bx, int by, 
   return CLUE_OK;
 }
 
-// Workgroups of k_units for a run of n hits (each takes 1024 hits at a time) in
-// one event, or for the batched form with n = 0 any run up to its capacity; 0
-// when the unit path is not to be tried: the depth-first expansion walks the
-// general path's lists, a layer's tile counts have to fit in LDS, and so do
-// most units.
-static int units_grid(const Geom& g, int64_t n, int64_t capacity) {
-  if (g.expand || g.tpl > kUnitTiles || n > (int64_t)g.L * kUnitAvg) return 0;
-  if (n == 0) n = capacity;
-  return (int)(std::max<int64_t>(1, std::min<int64_t>((n + 1023) / 1024, 1024) + kQueues - 1) / kQueues * kQueues);
+// Workgroups of k_units for a run of n hits in `units` units, or for the batched
+// form with units = 0 any run of up to n hits (the device then looks at the sizes);
+// 0 when the unit path is not to be tried: the depth-first expansion walks the
+// general path's lists, a layer's tile counts have to fit in LDS, and so do most
+// units.
+static int units_grid(const Geom& g, int64_t n, int64_t units) {
+  if (g.expand || g.tpl > kUnitTiles || (units && !unit_sizes(g, n, units))) return 0;
+  return (int)((std::max<int64_t>(1, std::min<int64_t>((n + 1023) / 1024, 1024)) + kQueues - 1) / kQueues * kQueues);
 }
 
 // Geometry that a run of n hits in `units` layers uses when no tuning is set
@@ -423,7 +422,7 @@ static int ensure_graph(clue_ctx* c) {
   RunDesc d{};
   d.n = (int32_t)c->a.cap_hits;
   d.n_events = c->a.cap_events;
-  c->g_batch.units = units_grid(c->g_batch, 0, c->a.cap_hits);
+  c->g_batch.units = units_grid(c->g_batch, c->a.cap_hits, 0);
   LaunchCfg cfg = c->cfg;
   cfg.graph_mode = true;
   HIP_TRY(c, hipStreamBeginCapture(c->cap_stream, hipStreamCaptureModeThreadLocal));
@@ -625,12 +624,12 @@ static int run_common(clue_ctx* c, int64_t n, int32_t n_events, int32_t event_ba
   } else if (sized) {
     LaunchCfg cfg = c->cfg;
     cfg.graph_mode = false;
-    c->g_plain.units = units_grid(c->g_plain, batched ? 0 : n, n);
+    c->g_plain.units = units_grid(c->g_plain, n, (int64_t)n_events * c->g_plain.L);
     HIP_TRY(c, launch_pipeline(c->g_plain, c->a, d, cfg, s, ev));
   } else {
     HIP_TRY(c, launch_set_desc(d, c->a.desc, s));
     if (ev) {
-      c->g_batch.units = units_grid(c->g_batch, 0, c->a.cap_hits);
+      c->g_batch.units = units_grid(c->g_batch, c->a.cap_hits, 0);
       LaunchCfg cfg = c->cfg;
       cfg.graph_mode = true;
       HIP_TRY(c, launch_pipeline(c->g_batch, c->a, d, cfg, s, ev));
@@ -1095,7 +1094,7 @@ int clue_run_noalloc(const clue_params* p, const clue_tuning* t, int64_t n, cons
   // contents do not matter
   LaunchCfg cfg{};
   cfg.graph_mode = false;
-  g.units = units_grid(g, n, n);
+  g.units = units_grid(g, n, g.L);
   if (g.expand) {  // the k-way walk's grid: one run of workgroups per XCD
     int ncu = 0;
     e = hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, dev);

@@ -149,7 +149,7 @@ __host__ __device__ __forceinline__ bool unit_space(const Geom& g, const RunDesc
   const int64_t n = d.n, U = (int64_t)d.n_events * g.L, side = 2 * g.halo + 1;
   const int64_t spill = n * side * side / g.lds_cap + n / kWG + 1;
   return spill + 2 * U + 1 <= n && g.units <= n && (int64_t)g.L * kUnitMax <= (int64_t)kPackedEventMax &&
-         n <= U * kUnitAvg;
+         unit_sizes(g, n, U);
 }
 __host__ __device__ __forceinline__ int32_t* unit_starts(const Arena& a, const RunDesc& d, const Geom& g) {
   return a.key + ((int64_t)d.n - (int64_t)d.n_events * g.L - 1);

@@ -387,6 +387,7 @@ __global__ __launch_bounds__(kUWG, 8) void k_unit_finish(DescArg<G> dg, Geom g, 
   const int U = d.n_events * g.L;
   const int32_t* const us = unit_starts(a, d, g);
   const int32_t* const uc = unit_counts(a, d, g);
+  int prev = 0, sb = 0, fb = 0;  // seeds of the event and followers of the run before unit prev
   for (int u = blockIdx.x; u < U; u += gridDim.x) {
     // in scalar registers, so that the accesses below take a scalar base
     const int s0 = __builtin_amdgcn_readfirstlane(us[u]), m = __builtin_amdgcn_readfirstlane(us[u + 1]) - s0;
@@ -401,16 +402,20 @@ __global__ __launch_bounds__(kUWG, 8) void k_unit_finish(DescArg<G> dg, Geom g, 
 #pragma unroll
     for (int k = 0; k < kUPer; ++k)
       if (k * kUWG < m) lk[k] = upar[(unsigned)min(k * kUWG + tid, m - 1)] - s0;
-    int sb = 0, fb = 0;  // seeds of the event and followers of the run in earlier units
-    for (int v = tid; v < u; v += kUWG) {
-      if (v >= u0) sb += uc[2 * v];
-      fb += uc[2 * v + 1];
+    // the counts since this workgroup's previous unit, so that a run's units cost it
+    // one pass over their counts (added up from the first for each of 100,000 units,
+    // they took 3.2 ms)
+    int ds = 0, df = 0;
+    for (int v = prev + tid; v < u; v += kUWG) {
+      if (v >= u0) ds += uc[2 * v];
+      df += uc[2 * v + 1];
     }
     for (int i = tid; i < W; i += kUWG) s_seed[i] = 0u;
-    wg_excl(sb, s_part, sb);
-    wg_excl(fb, s_part, fb);
-    sb = __builtin_amdgcn_readfirstlane(sb);
-    fb = __builtin_amdgcn_readfirstlane(fb);
+    wg_excl(ds, s_part, ds);
+    wg_excl(df, s_part, df);
+    sb = (prev < u0 ? 0 : sb) + __builtin_amdgcn_readfirstlane(ds);
+    fb += __builtin_amdgcn_readfirstlane(df);
+    prev = u;
     tid = fresh(tid);
 #pragma unroll
     for (int k0 = 0; k0 < kUPer; k0 += V) {
