@@ -215,11 +215,14 @@ static int units_grid(const Geom& g, int64_t n, int64_t units) {
 //
 // Sparse layers: tiles grow by up to a quarter towards 1.8 hits each, because a
 // tile costs its share of the grid and of the quad lists whether or not it holds
-// hits (16 events of 100 layers of 300 hits: 337 us, grown 238; of 1400: 411 and
-// 326; one event of 1000 a layer: 80 and 79). Not further, for a query's lists grow
-// with the tile's area where a layer's hits lie close together (60 % of 1900 hits
-// within 20 cm: 314 us, 253 grown by a quarter, 448 by a half), and only where a
-// layer holds at most twice the cap on average (3000 hits a layer gain nothing).
+// hits (16 events of 100 layers of 300 uniform hits: 316 us, grown 215; of 1400: 361
+// and 284). Not further, for a query's lists grow with the tile's area where a layer's
+// hits lie close together, and only where a layer holds at most twice the cap on
+// average (3000 hits a layer gain nothing). And only in runs of at least as many
+// layers as the GPU has CUs: a run of fewer waits for the workgroups of its fullest
+// spots. 100 layers of 1000 hits, 90 % of them within 10 cm: 362 us, grown 492, with
+// the requested 8 x 8 blocks of 4 cm tiles 404; uniform, 72 and 69. 200 layers of
+// them: 382 and 542; uniform, 96 and 84.
 //
 // Block: as many tiles a side as make its region (block and halo) hold 620 hits
 // on average, at most 24 with the halo. At the default cap of 960 hits, that
@@ -234,7 +237,7 @@ static int units_grid(const Geom& g, int64_t n, int64_t units) {
 // layers of 1900 hits: 93 us with 900 blocks, 102 with 400).
 static Geom run_geom(const clue_params& p, const Geom& req, int tpq, int lds_cap, float r1, int quads,
                      int expansion, double n, double units) {
-  constexpr double kRegionHits = 620.0, kTileHits = 1.8;
+  constexpr double kRegionHits = 620.0, kTileHits = 1.8, kCUs = 256.0;
   std::string msg;
   float tile = p.tile_size;
   Geom g = req;
@@ -243,7 +246,7 @@ static Geom run_geom(const clue_params& p, const Geom& req, int tpq, int lds_cap
     tile = two;
     if (plan_geom(p, tile, tpq, 1, 1, lds_cap, r1, quads, expansion, g, msg) != CLUE_OK) return req;
   }
-  if (n <= units * 2.0 * lds_cap) {
+  if (units >= kCUs && n <= units * 2.0 * lds_cap) {
     const double grow = std::min(1.25, std::sqrt(kTileHits * units * g.tpl / std::max(n, 1.0)));
     if (grow > 1.0) {
       tile = (float)(grow / (double)g.inv_t);

@@ -1,6 +1,8 @@
 // Host check of the geometry that untuned runs take (no GPU): over many extents,
 // distances and requested tiles it never needs more tiles than the requested one,
-// which the arena is sized for, and stays within what the kernels stage.
+// which the arena is sized for, stays within what the kernels stage, and keeps the
+// requested tile where a run has few layers (one crowded spot in each is then what
+// it waits for, and a query's lists grow with the tile).
 #include "clue_api.hip"
 
 #include <random>
@@ -38,7 +40,7 @@ int main() {
     p.y_min = (float)(i % 2 ? oy : -oy);
     p.x_max = (float)(ox + wx);
     p.y_max = (float)(p.y_min + wy);
-    p.n_layers = 1 + i % 100;
+    p.n_layers = 1 + i % 400;
     p.tile_size = i % 4 ? (float)(p.dc * uni(1.0, 6.0)) : 0.0f;
     Geom req{};
     std::string msg;
@@ -54,6 +56,8 @@ int main() {
                          : g.maxl > req.maxl ? "a density window of more tiles"
                          : rh > kMaxRegionRows || rh * (rw + 1) > kMaxRegionTiles || g.ts_ints < rh * (rw + 1) + 1
                              ? "a region over the staged limit"
+                         : req.maxl == 2 && units < 256.0 && g.inv_t != req.inv_t
+                             ? "a grown tile in a run of fewer layers than CUs"
                          : g.bx > 24 || g.by > 24 || g.bx < 1 || g.by < 1 ? "a block over the walk's limit"
                                                                           : nullptr;
       if (what) {
