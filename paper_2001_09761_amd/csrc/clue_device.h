@@ -57,6 +57,25 @@ __device__ __forceinline__ int wave_incl_scan(int v, int lane) {
   }
   return v;
 }
+// Exclusive sum over a workgroup of T lanes, and the total. `tid` is the lane's
+// thread id; s_part holds T / 64 words.
+template <int T>
+__device__ __forceinline__ int wg_excl(int v, int* s_part, int& total, int tid) {
+  const int lane = tid & 63, wave = tid >> 6;
+  const int incl = wave_incl_scan(v, lane);
+  __syncthreads();
+  if (lane == 63) s_part[wave] = incl;
+  __syncthreads();
+  int base = 0, all = 0;
+#pragma unroll
+  for (int w = 0; w < T / 64; ++w) {
+    const int s = s_part[w];
+    base += w < wave ? s : 0;
+    all += s;
+  }
+  total = all;
+  return base + incl - v;
+}
 __device__ __forceinline__ int wave_sum(int v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);

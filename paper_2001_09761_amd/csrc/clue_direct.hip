@@ -347,23 +347,6 @@ constexpr int kFinWords = kDirectMax / 32 + 1;
 static_assert(kDirectMax <= 65535, "links, counts and list entries are 16-bit");
 static_assert(kFinWords <= kFinWG, "one lane per bitmap word");
 
-// Exclusive sum over the workgroup, and the total in *total.
-__device__ __forceinline__ int wg_excl_sum(int v, int* s_part, int* total) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int incl = wave_incl_scan(v, lane);
-  __syncthreads();
-  if (lane == 63) s_part[wave] = incl;
-  __syncthreads();
-  int base = 0, all = 0;
-  for (int w = 0; w < kFinWG / 64; ++w) {
-    const int s = s_part[w];
-    base += w < wave ? s : 0;
-    all += s;
-  }
-  *total = all;
-  return base + incl - v;
-}
-
 template <int PER>
 __global__ __launch_bounds__(kFinWG) void k_direct_finish(RunDesc d, Geom g, Arena a) {
   // dynamic LDS, 16 bits each: list entries, then links [n]; follower counts, then offsets [n + 1]
@@ -408,7 +391,7 @@ __global__ __launch_bounds__(kFinWG) void k_direct_finish(RunDesc d, Geom g, Are
     const int words = n / 32 + 1;
     const unsigned ws = tid < words ? s_seed[tid] : 0u, wf = tid < words ? s_first[tid] : 0u;
     int total;
-    const int r = wg_excl_sum(__popc(ws), s_part, &total);
+    const int r = wg_excl<kFinWG>(__popc(ws), s_part, total, tid);
     if (tid < words) {
       s_wrank[tid] = r;
       s_wfirst[tid] = 0;
@@ -454,7 +437,7 @@ __global__ __launch_bounds__(kFinWG) void k_direct_finish(RunDesc d, Geom g, Are
       v[k] = i0 + k < n ? off[i0 + k] : 0;
       sum += v[k];
     }
-    int run = wg_excl_sum(sum, s_part, &total);
+    int run = wg_excl<kFinWG>(sum, s_part, total, tid);
 #pragma unroll
     for (int k = 0; k < PER; ++k) {
       if (i0 + k < n) off[i0 + k] = (unsigned short)run;

@@ -56,24 +56,6 @@ __device__ __forceinline__ int fresh(int v) {
   return v;
 }
 
-// Exclusive sum over the workgroup, and the total. `tid` is the lane's thread id.
-__device__ __forceinline__ int wg_excl(int v, int* s_part, int& total, int tid) {
-  const int lane = tid & 63, wave = tid >> 6;
-  const int incl = wave_incl_scan(v, lane);
-  __syncthreads();
-  if (lane == 63) s_part[wave] = incl;
-  __syncthreads();
-  int base = 0, all = 0;
-#pragma unroll
-  for (int w = 0; w < kUWG / 64; ++w) {
-    const int s = s_part[w];
-    base += w < wave ? s : 0;
-    all += s;
-  }
-  total = all;
-  return base + incl - v;
-}
-
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -266,7 +248,7 @@ __global__ __launch_bounds__(kUWG, 8) void k_unit_sort(DescArg<G> dg, Geom g, Ar
     {
       const int c0 = lo & 0xffffu, c1 = hi & 0xffffu, c2 = lo >> 16, c3 = hi >> 16;
       int total;
-      const int b0 = wg_excl(c0 + c1 + c2 + c3, s_part, total, fresh(tid));
+      const int b0 = wg_excl<kUWG>(c0 + c1 + c2 + c3, s_part, total, fresh(tid));
       const int b1 = b0 + c0, b2 = b1 + c1, b3 = b2 + c2;
       if (tid < tw) {
         start[4 * tid] = (unsigned short)b0;
@@ -411,8 +393,8 @@ __global__ __launch_bounds__(kUWG, 8) void k_unit_finish(DescArg<G> dg, Geom g, 
       df += uc[2 * v + 1];
     }
     for (int i = tid; i < W; i += kUWG) s_seed[i] = 0u;
-    wg_excl(ds, s_part, ds, threadIdx.x);
-    wg_excl(df, s_part, df, threadIdx.x);
+    wg_excl<kUWG>(ds, s_part, ds, threadIdx.x);
+    wg_excl<kUWG>(df, s_part, df, threadIdx.x);
     sb = (prev < u0 ? 0 : sb) + __builtin_amdgcn_readfirstlane(ds);
     fb += __builtin_amdgcn_readfirstlane(df);
     prev = u;
@@ -443,7 +425,7 @@ __global__ __launch_bounds__(kUWG, 8) void k_unit_finish(DescArg<G> dg, Geom g, 
     {
       const int c = tid < W ? __popc(s_seed[tid]) : 0;
       int total;
-      const int r = wg_excl(c, s_part, total, threadIdx.x);
+      const int r = wg_excl<kUWG>(c, s_part, total, threadIdx.x);
       if (tid < W) s_rank[tid] = r;
     }
     __syncthreads();
@@ -503,7 +485,7 @@ __global__ __launch_bounds__(kUWG, 8) void k_unit_finish(DescArg<G> dg, Geom g, 
       const int i0 = min(tid * per, m + 1), i1 = min(i0 + per, m + 1);
       int sum = 0, total;
       for (int i = i0; i < i1; ++i) sum += i < m ? off[i] : 0;
-      int run = wg_excl(sum, s_part, total, threadIdx.x);
+      int run = wg_excl<kUWG>(sum, s_part, total, threadIdx.x);
       for (int i = i0; i < i1; ++i) {
         const int c = i < m ? off[i] : 0;
         off[i] = (unsigned short)run;
