@@ -567,7 +567,7 @@ static int validate_inputs(clue_ctx* c, const RunDesc& d, hipStream_t s) {
 
 constexpr int64_t kSizedMaxHits = 1 << 22;   // hits, and work items, of the largest batch that
 constexpr int64_t kSizedMaxItems = 1 << 16;  // is run by launches sized to it
-constexpr int64_t kPlainCapHits = 1 << 21;   // ... and hits of the largest with the plain form's LDS cap
+constexpr int64_t kPlainCapHits = 1 << 21;   // hits of the largest event with the plain form's LDS cap
 
 static int run_common(clue_ctx* c, int64_t n, int32_t n_events, int32_t event_base, const int32_t* event,
                       const float* x, const float* y, const int32_t* layer, const float* energy, int32_t* cid,
@@ -594,8 +594,12 @@ static int run_common(clue_ctx* c, int64_t n, int32_t n_events, int32_t event_ba
   const bool sized = !batched || (n <= kSizedMaxHits && (int64_t)n_events * gr.L * gr.bpu <= kSizedMaxItems);
   if (sized) {
     c->g_plain = gr;
-    // the plain form may stage a different number of hits per work item
-    if (c->plain_cap > 0 && n <= kPlainCapHits) c->g_plain.lds_cap = c->plain_cap;
+    // One event has few work items in flight and may stage more hits in each (a
+    // tuned event of 1M hits 171 us at a cap of 960, 179 at 800). Batches of several
+    // keep lds_cap, as more workgroups then fit a CU: 16 events of 100 layers of 300
+    // hits 442 us at 800, 537 at 1024; 4 of 5000 hits a layer 250, 275 at 960. So
+    // does one event of more than 2M hits: 2.5M 465 us at 800, 492 at 1024.
+    if (c->plain_cap > 0 && n_events == 1 && n <= kPlainCapHits) c->g_plain.lds_cap = c->plain_cap;
   }
   d.n = (int32_t)n;
   d.n_events = n_events;
