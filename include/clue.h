@@ -141,7 +141,8 @@ int clue_run(clue_ctx *c, int64_t n, const float *x, const float *y, const int32
  * all layers of one event in each kernel launch; this extends that to many
  * events: one persistent kernel per stage over a device work queue of
  * (event, layer, tile block) items, replayed from a captured HIP graph. Small
- * batches (up to 4M hits) are launched as clue_run is, sized to the batch.
+ * batches (up to 4M hits and 65,536 items) are launched as clue_run is, sized to
+ * the batch.
  * Errors as clue_run, plus CLUE_ERR_ARG for a null `event` with n_events > 1;
  * ids out of range or decreasing are caught only with CLUE_VALIDATE (without
  * it the run stays within its buffers, with unspecified results).
@@ -241,7 +242,11 @@ typedef struct {
  * (the context keeps its previous tuning). */
 int clue_set_tuning(clue_ctx *c, const clue_tuning *t);
 
-/* Current tuning, and the staged halo width in tiles it implies. */
+/* Current tuning, and the staged halo width in tiles it implies: what clue_set_tuning
+ * has set, and the requested tile and the defaults elsewhere. Every run uses it once
+ * clue_set_tuning has been called. Until then runs of more than 8192 hits take their
+ * tile and block (and so the halo) from their occupancy, with these as the starting
+ * point, and smaller runs use neither. */
 int clue_get_tuning(const clue_ctx *c, clue_tuning *t, int32_t *halo);
 
 /* Bytes of device scratch the no-allocation form holds per device. */

@@ -38,10 +38,12 @@ constexpr int kBatchU = 8;         // ... and of the batched k_scatter, k_place 
                                    // or a parent chain on chip (single launches keep kPlaceU, for more
                                    // workgroups per event)
 constexpr int kDirectMax = 8192;   // hits of the largest run that takes the all-pairs form
+// The unit path. kUnitMax and kUnitTiles are what leaves two of its workgroups on a
+// CU: a column of the unit, the slots' hits and the tile offsets are 73 KB of LDS.
 constexpr int kUnitMax = 11264;      // hits of the largest unit the unit path takes
-constexpr int kUnitAvg = 10240;      // ... and of the largest mean unit it is tried for
 constexpr int kUnitTiles = 2816;     // tiles of the largest layer grid it takes
-constexpr int kUnitFew = 768;        // units that it takes however few hits they hold
+constexpr int kUnitAvg = 10240;      // hits of the largest mean unit it is tried for (unit_sizes)
+constexpr int kUnitFew = 768;        // units that it takes however few hits they hold (unit_sizes)
 constexpr int kScatterBlocksPerCU = 2;  // persistent k_scatter workgroups per CU
 
 // Counters in device memory, cleared at the start of every run. Each sits on
@@ -119,14 +121,22 @@ struct Geom {
 // or when the depth-first expansion walks them.
 __host__ __device__ inline bool builds_lists(const Geom& g) { return !(g.flags & 8u) || g.expand != 0; }
 
-// Whether the sizes of a run, n hits in U units, suit the unit path. A unit costs a
-// workgroup 10 us or so however few hits it holds; the general path pays by the hit
-// and by the tile. So where a workgroup has more than one unit or two, thin units go
-// the general way. Batches by units and in general: 600 units of 100 hits 111 and 117
-// us (1,600 tiles a layer), 78 and 82 us (100 tiles); 1,600 units of 300 hits 220 and
-// 216, 143 and 129 us; 6,400 units of 300, 400 and 600 hits and 1,600 tiles 698, 710
-// and 746 against 660, 718 and 832 us; 6,400 units of 400, 600 and 800 hits and 100
-// tiles 422, 648 and 771 against 336, 613 and 792 us.
+// Whether the sizes of a run, n hits in U units, suit the unit path.
+//
+// Full units: one of more than kUnitMax hits sends the whole run the general way, so
+// the path is tried where the mean leaves the fullest unit a tenth above it. Trying in
+// vain costs up to 4 %, and layers that are equal up to kUnitMax would gain as they do
+// below the line: one event of 100 layers of 10,240 hits 166 us by units, of 10,500
+// 242 us in general, 166 by units, 251 where one layer of 11,500 rules them out; 16
+// such events 1,369, 2,986, 1,404 and 3,048 us.
+//
+// Thin units: a unit costs a workgroup 10 us or so however few hits it holds; the
+// general path pays by the hit and by the tile. So where a workgroup has more than one
+// unit or two, they go the general way. Batches by units and in general: 600 units of
+// 100 hits 111 and 117 us (1,600 tiles a layer), 78 and 82 us (100 tiles); 1,600 units
+// of 300 hits 220 and 216, 143 and 129 us; 6,400 units of 300, 400 and 600 hits and
+// 1,600 tiles 698, 710 and 746 against 660, 718 and 832 us; 6,400 units of 400, 600
+// and 800 hits and 100 tiles 422, 648 and 771 against 336, 613 and 792 us.
 __host__ __device__ inline bool unit_sizes(const Geom& g, int64_t n, int64_t U) {
   return n <= U * kUnitAvg && (U <= kUnitFew || n >= U * (700 - g.tpl / 5));
 }

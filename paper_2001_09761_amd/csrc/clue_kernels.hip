@@ -1863,8 +1863,9 @@ __global__ __launch_bounds__(kWG) void k_nh_spill(DescArg<G> dg, Geom g, Arena a
 // of an event that comes layer by layer span less, and are staged all the same: 2.5M
 // hits in 100 layers, 12.2 ms when every region was searched in global memory, 1.23
 // when each was spilled, 0.23 now. It is an instance of its own because the same code
-// in the others made nearest-higher of other runs 2% slower; a batch, whose events'
-// sizes the host does not know, spills such an event.
+// in the others made nearest-higher of other runs 2% slower. The host takes it for
+// runs of one event, but for an event of more than 4M hits in a batch, which the
+// captured graph runs: that one, and one in a batch of several, is spilled.
 template <bool G, bool STRICT, bool LARGE = false>
 __global__ __launch_bounds__(kWG, 8) void k_nearest_higher(DescArg<G> dg, Geom g, Arena a) {
   __shared__ int s_counts[2];
