@@ -19,8 +19,8 @@
 // each; merging the general stages into fewer launches with waits between their
 // chunks cost such runs 36 us a wait, in L2 write-backs).
 //
-// What it measured, 32 events of 1M hits: grid build 846 -> 345 us (copying its
-// inputs and outputs alone would take 240), labels and lists 617 -> 261 us, and
+// What it measured, 32 events of 1M hits: grid build 846 -> 338 us (copying its
+// inputs and outputs alone would take 240), labels and lists 617 -> 258 us, and
 // the nearest-higher stage 1,025 -> 955 us without the follower-count atomics.
 // The grid build is bound by the latency of its phases (count, scan, place, three
 // columns), which two units per CU overlap; the finish by that of its LDS chases.
